@@ -101,7 +101,7 @@ int enqueue_batched(epr_ctx* h, hipStream_t cs, std::vector<epr_ctx::EvPair>* si
             const int order = (k == kBsWkb1Split || k == kBsWkb1Lines) ? kOrderTransportWkb1
                                                                         : bp.order;
             rc = run_stage(h, kStLocal, gs, sk, [&] {
-              return launch_local(a, grid, lds_local(bp.L), gs, order);
+              return launch_local(a, grid, gs, order, bp.L, G.lrows);
             }, cls);
             break;
           }
@@ -304,6 +304,12 @@ int solve_batched_impl(epr_ctx* h, int32_t n, const epr_problem* problems,
       G.rl = row_lines(descs[first]);
       G.ny_max = 0;
       for (int i = 0; i < cnt; ++i) G.ny_max = std::max(G.ny_max, descs[first + i].ny);
+      int b16 = 0;  // one strip height per launch
+      for (int i = 0; i < cnt; ++i)
+        b16 += blocks_local_rows(descs[first + i].ny, descs[first + i].nx, L, 16);
+      G.lrows = local_rows(b16, L);
+      for (int i = 0; i < cnt; ++i) descs[first + i].lrows = G.lrows;
+      if (g == bp.resid_group) bp.resid_desc.lrows = G.lrows;
       start_off[g] = starts.size();
       for (int st_i = 0; st_i < bp.ns; ++st_i) {
         int acc = 0;

@@ -100,13 +100,13 @@ int epr_forward(epr_handle h, const epr_geometry* geom, const epr_spectrum* spec
   } else if (model == EPR_NONLOCAL_L2) {
     CHECK(launch_transport_lines(h, p, st, cls));
     CHECK(run_stage(h, kStLocal, st, &h->pending, [&] {
-      return launch_local(single(p, kLocalForward), blocks_local(p), lds_local(lp.n), st,
-                          kOrderTransportWkb1);
+      return launch_local(single(p, kLocalForward), blocks_local(p), st,
+                          kOrderTransportWkb1, p.lp.n, p.lrows);
     }, cls));
   } else {
     CHECK(run_stage(h, kStLocal, st, &h->pending, [&] {
-      return launch_local(single(p, kLocalForward), blocks_local(p), lds_local(lp.n), st,
-                          model == EPR_LOCAL_L1 ? 1 : 2);
+      return launch_local(single(p, kLocalForward), blocks_local(p), st,
+                          model == EPR_LOCAL_L1 ? 1 : 2, p.lp.n, p.lrows);
     }, cls));
   }
   h->last_stream = st;
@@ -244,13 +244,13 @@ int epr_forward_xspec(epr_handle h, const epr_geometry* geom, const epr_spectrum
   } else if (model == EPR_NONLOCAL_L2) {
     CHECK(launch_transport_lines(h, p, st, cls));
     CHECK(run_stage(h, kStLocal, st, &h->pending, [&] {
-      return launch_local(single(p, kLocalForward), blocks_local(p), lds_local(L), st,
-                          kOrderTransportWkb1);
+      return launch_local(single(p, kLocalForward), blocks_local(p), st,
+                          kOrderTransportWkb1, p.lp.n, p.lrows);
     }, cls));
   } else {
     CHECK(run_stage(h, kStLocal, st, &h->pending, [&] {
-      return launch_local(single(p, kLocalForward), blocks_local(p), lds_local(L), st,
-                          model == EPR_LOCAL_L1 ? 1 : 2);
+      return launch_local(single(p, kLocalForward), blocks_local(p), st,
+                          model == EPR_LOCAL_L1 ? 1 : 2, p.lp.n, p.lrows);
     }, cls));
   }
   h->last_stream = st;

@@ -84,6 +84,7 @@ struct ProbDesc {
   int ny, nx;
   int nblk;           // ceil((nx/2 + 1) / kColBlock)
   int splat_tx, splat_ty;
+  int lrows;          // local closure: rows per strip (4, 8 or 16)
   const float* X;
   const float* Y;
   const float* d;
@@ -160,10 +161,26 @@ __host__ __device__ inline int blocks_colfft(const ProbDesc& p) { return p.nblk 
 __host__ __device__ inline int blocks_rowinv(const ProbDesc& p) {
   return (p.ny + kRows - 1) / kRows;
 }
-constexpr int kLocalTile = 16;  // local closure: 16 x 16 outputs per workgroup
+// Local closure: one wave per line and strip of kLocalCols x lrows outputs (kLocalHalo halo
+// columns on either side fill the wave's 64 lanes); a workgroup holds local_strips(L) strips of
+// all L lines, side by side.
 constexpr int kLocalHalo = 4;
+constexpr int kLocalCols = 64 - 2 * kLocalHalo;
+__host__ __device__ inline int local_strips(int lines) { return lines >= 3 ? 1 : lines == 2 ? 2 : 4; }
+__host__ __device__ inline int blocks_local_rows(int ny, int nx, int lines, int rows) {
+  const int cols = local_strips(lines) * kLocalCols;
+  return ((ny + rows - 1) / rows) * ((nx + cols - 1) / cols);
+}
 __host__ __device__ inline int blocks_local(const ProbDesc& p) {
-  return ((p.ny + kLocalTile - 1) / kLocalTile) * ((p.nx + kLocalTile - 1) / kLocalTile);
+  return blocks_local_rows(p.ny, p.nx, p.lp.n, p.lrows);
+}
+// Rows per strip of a launch that takes blocks16 workgroups at 16 rows: 16 (1.5 rows computed
+// per output row) where that still gives every SIMD a wave (1024 on the chip), else 8 (2 rows per
+// output row, but twice the waves, each half as long), and 4 where even that leaves most SIMDs
+// idle.  With 16 lines, 16 rows would need more than 64 KB of LDS.
+inline int local_rows(int blocks16, int lines) {
+  const int waves = blocks16 * lines * local_strips(lines);
+  return waves < 256 ? 4 : (waves < 1024 || lines >= 16) ? 8 : 16;
 }
 // detector-level residual on an oversampled grid: one detector pixel per thread, 256 threads
 __host__ __device__ inline int blocks_binsplit(const ProbDesc& p) {
@@ -197,7 +214,8 @@ constexpr int kColMidMax = 2304;
 // dynamic LDS bytes. They return the hipError_t of the launch.
 hipError_t launch_maxgrad(const KArgs& a, int total_blocks, hipStream_t s);
 hipError_t launch_splat(const KArgs& a, int total_blocks, size_t lds, hipStream_t s, int lines);
-hipError_t launch_local(const KArgs& a, int total_blocks, size_t lds, hipStream_t s, int order);
+hipError_t launch_local(const KArgs& a, int total_blocks, hipStream_t s, int order, int lines,
+                        int rows);
 hipError_t launch_rowfft(const KArgs& a, int total_blocks, size_t lds, hipStream_t s, int nt);
 hipError_t launch_colfft(const KArgs& a, int total_blocks, size_t lds, hipStream_t s, int nt);
 hipError_t launch_rowinv(const KArgs& a, int total_blocks, size_t lds, hipStream_t s, int nt);
@@ -217,7 +235,6 @@ hipError_t launch_vjp_local(const KArgs& a, int total_blocks, hipStream_t s, int
 hipError_t launch_vjp_transpose(const KArgs& a, int total_blocks, hipStream_t s,
                                 const float* gx, const float* gy, float* gphase,
                                 int accumulate);
-size_t lds_local(int n_lines);
 // Fixed scratch of the allocation-free solve (noalloc.hip): the device address of this GPU's
 // copy of the scratch array (`device` must be the current device on the first call for it),
 // and a W_n^j table (j < n) written into it by a kernel.
@@ -225,7 +242,6 @@ hipError_t noalloc_scratch_address(int device, void** out);
 hipError_t launch_twiddle_table(float2* out, int n, hipStream_t s);
 hipError_t set_transport_attributes();
 hipError_t set_spectral_attributes();
-hipError_t set_local_attributes();
 hipError_t set_vjp_attributes();
 
 }  // namespace epr

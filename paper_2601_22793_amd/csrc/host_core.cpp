@@ -413,8 +413,12 @@ WsLayout ws_layout(int ny, int nx, int L, int tx, int ty) {
   w.e = align256(sizeof(float) * (size_t)L * ny * nx);
   w.spec = align256(sizeof(float2) * (size_t)L * nblk * ny * kColBlock);
   w.maxg = align256(sizeof(float) * 3 * kMaxgBlocks);
-  const size_t nb = (size_t)((ny + ty - 1) / ty) * ((nx + tx - 1) / tx);
-  w.resid = align256(sizeof(float) * 2 * std::max(nb, (size_t)((ny + 15) / 16) * ((nx + 15) / 16)));
+  // residual partials: one pair per workgroup of the stage that forms the residual
+  const size_t nb = std::max((size_t)((ny + ty - 1) / ty) * ((nx + tx - 1) / tx),
+                             (size_t)((ny + 15) / 16) * ((nx + 15) / 16));
+  // (a batch takes strips at least as high as the problem alone)
+  const int rows = local_rows(blocks_local_rows(ny, nx, L, 16), L);
+  w.resid = align256(sizeof(float) * 2 * std::max(nb, (size_t)blocks_local_rows(ny, nx, L, rows)));
   w.total = w.e + w.spec + w.maxg + w.resid;
   return w;
 }
@@ -450,6 +454,7 @@ int fill_desc(epr_ctx* h, const epr_geometry& g, const LineParams& lp, char* bas
   p->nblk = (g.nx / 2 + 1 + kColBlock - 1) / kColBlock;
   p->splat_tx = h->splat_tx;
   p->splat_ty = h->splat_ty;
+  p->lrows = local_rows(blocks_local_rows(g.ny, g.nx, lp.n, 16), lp.n);
   p->lp = lp;
   p->os = 1;
   WsLayout w = ws_layout(g.ny, g.nx, lp.n, h->splat_tx, h->splat_ty);
@@ -505,13 +510,13 @@ int launch_lines_binsplit(epr_ctx* h, const ProbDesc& p, int model, hipStream_t 
     rc = launch_transport_lines(h, p, st, cls);
     if (rc) return rc;
     rc = run_stage(h, kStLocal, st, sink, [&] {
-      return launch_local(single(p, kLocalLines), blocks_local(p), lds_local(p.lp.n), st,
-                          kOrderTransportWkb1);
+      return launch_local(single(p, kLocalLines), blocks_local(p), st,
+                          kOrderTransportWkb1, p.lp.n, p.lrows);
     }, cls);
   } else {
     rc = run_stage(h, kStLocal, st, sink, [&] {
-      return launch_local(single(p, kLocalLines), blocks_local(p), lds_local(p.lp.n), st,
-                          model == EPR_LOCAL_L1 ? 1 : 2);
+      return launch_local(single(p, kLocalLines), blocks_local(p), st,
+                          model == EPR_LOCAL_L1 ? 1 : 2, p.lp.n, p.lrows);
     }, cls);
   }
   if (rc) return rc;
@@ -540,8 +545,8 @@ int launch_iteration(epr_ctx* h, const ProbDesc& p, int model, hipStream_t st, f
     rc = launch_transport_lines(h, p, st, cls);
     if (rc) return rc;
     rc = run_stage(h, kStLocal, st, sink, [&] {
-      return launch_local(single(p, kLocalSplit), blocks_local(p), lds_local(p.lp.n), st,
-                          kOrderTransportWkb1);
+      return launch_local(single(p, kLocalSplit), blocks_local(p), st,
+                          kOrderTransportWkb1, p.lp.n, p.lrows);
     }, cls);
     if (rc) return rc;
     if (hist_slot) HIP_TRY(h, launch_resid_reduce(single(p, 0), hist_slot, blocks_local(p), st));
@@ -564,8 +569,8 @@ int launch_iteration(epr_ctx* h, const ProbDesc& p, int model, hipStream_t st, f
     if (rc) return rc;
   } else {
     rc = run_stage(h, kStLocal, st, sink, [&] {
-      return launch_local(single(p, kLocalSplit), blocks_local(p), lds_local(p.lp.n), st,
-                          model == EPR_LOCAL_L1 ? 1 : 2);
+      return launch_local(single(p, kLocalSplit), blocks_local(p), st,
+                          model == EPR_LOCAL_L1 ? 1 : 2, p.lp.n, p.lrows);
     }, cls);
     if (rc) return rc;
     if (hist_slot) HIP_TRY(h, launch_resid_reduce(single(p, 0), hist_slot, blocks_local(p), st));
@@ -768,7 +773,6 @@ int epr_create(epr_handle* out, int device) {
   // support the attribute leaves the default; a launch needing more then fails and reports.
   (void)set_transport_attributes();
   (void)set_spectral_attributes();
-  (void)set_local_attributes();
   (void)set_vjp_attributes();
   (void)set_regime_attributes();
   (void)hipGetLastError();

@@ -5,11 +5,22 @@
 //       + 1/2 [D_x D_x(I u_x^2) + D_x D_y(I u_x u_y) + D_y D_x(I u_y u_x) + D_y D_y(I u_y^2)]
 //       - q_s [D_x(I D_x Q) + D_y(I D_y Q)],     Q = (D_x D_x A + D_y D_y A) / A,
 // with D the central difference inside the image and the one-sided difference on its edges,
-// exactly as the composition of derivatives is written in Eq. 1.  Order 1 keeps the first
-// bracket only.  Order 3 is the second-order non-local model: the transported prediction
-// M_s[I_s], already in e (the splat's per-line output), plus the diffraction-pressure term.  A workgroup owns a 16 x 16 output tile and evaluates the nested derivatives
-// on shrinking squares of a 24 x 24 LDS region (halo 4: Q needs A two pixels further out than
-// the outer derivative of the diffraction-pressure term, which is one pixel out).
+// exactly as the composition of derivatives is written in Eq. 1 (D_x and D_y commute, so the two
+// mixed terms are one, taken twice).  Order 1 keeps the first bracket only.  Order 3 is the
+// second-order non-local model: the transported prediction M_s[I_s], already in e (the splat's
+// per-line output), plus the diffraction-pressure term.
+//
+// One wave computes one line on a strip of kLocalCols output columns x R output rows, alone: each
+// lane owns one image column (kLocalHalo lanes of halo on either side), the column neighbours come
+// from the adjacent lanes with the wave-shift DPP modes, and the row neighbours stay in registers
+// as the wave moves down the R + 2 kLocalHalo rows (fully unrolled).  The nested derivatives so
+// need no LDS and no barrier; LDS only carries the finished P_s to the per-pixel sum over lines
+// at the end (one barrier).  A workgroup holds one wave per line and strip: local_strips(L)
+// strips of every line, so that few-line problems still fill a workgroup.
+//
+// Bound by vector issue (about 75 instructions per row, line and wave).  Against a version that
+// walked the levels of derivatives over 24 x 24 LDS regions with five barriers per line:
+// 1080 x 1200, 4 lines: 159 -> 29 us a launch; 256 x 256, 1 line: 8.4 -> 6.9 us.
 #include <hip/hip_runtime.h>
 
 #include "dev_common.h"
@@ -17,153 +28,194 @@
 
 namespace epr {
 
-constexpr int kLT = kLocalTile;
 constexpr int kLH = kLocalHalo;
-constexpr int kLR = kLT + 2 * kLH;  // region side (24)
-constexpr int kLN = kLR * kLR;
-constexpr int kLocalThreads = 256;
 
-// D along x / y of a region field at region point (ly, lx) whose image coordinate is (y, x).
-__device__ __forceinline__ float rdx(const float* F, int ly, int lx, int x, int nx) {
-  const float* row = F + ly * kLR;
-  if (x == 0) return row[lx + 1] - row[lx];
-  if (x == nx - 1) return row[lx] - row[lx - 1];
-  return 0.5f * (row[lx + 1] - row[lx - 1]);
+// value of the lane to the left (lane - 1) and to the right (lane + 1); the wave's first / last
+// lane reads zero (its column is halo, never an output)
+__device__ __forceinline__ float lane_left(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
 }
-__device__ __forceinline__ float rdy(const float* F, int ly, int lx, int y, int ny) {
-  if (y == 0) return F[(ly + 1) * kLR + lx] - F[ly * kLR + lx];
-  if (y == ny - 1) return F[ly * kLR + lx] - F[(ly - 1) * kLR + lx];
-  return 0.5f * (F[(ly + 1) * kLR + lx] - F[(ly - 1) * kLR + lx]);
+__device__ __forceinline__ float lane_right(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
 }
 
-// Iterate over the region points at halo level <= h that lie inside the image.
-#define FOR_LEVEL(h, BODY)                                                   \
-  {                                                                          \
-    const int side_ = kLT + 2 * (h);                                         \
-    for (int i_ = threadIdx.x; i_ < side_ * side_; i_ += kLocalThreads) {     \
-      const int ly = kLH - (h) + i_ / side_;                                 \
-      const int lx = kLH - (h) + i_ % side_;                                 \
-      const int y = ry0 + ly, x = rx0 + lx;                                  \
-      if (y < 0 || y >= ny || x < 0 || x >= nx) continue;                    \
-      const int o = ly * kLR + lx;                                           \
-      BODY                                                                   \
-    }                                                                        \
-    __syncthreads();                                                         \
-  }
-
-// XDEP: x-dependent spectrum, every line constant is read at the point's column.
-template <bool XDEP>
-__device__ __forceinline__ void local_body(const ProbDesc& p, int local, int mode, int order) {
-  extern __shared__ float sm[];
-  float* fI = sm;
-  float* fA = fI + kLN;
-  float* fDxA = fA + kLN;
-  float* fDyA = fDxA + kLN;
-  float* fQ = fDyA + kLN;
-  float* fIx = fQ + kLN;
-  float* fIy = fIx + kLN;
-  float* fPxx = fIy + kLN;
-  float* fPxy = fPxx + kLN;
-  float* fPyy = fPxy + kLN;
-  float* fGx = fPyy + kLN;
-  float* fGy = fGx + kLN;
-  float* fFxx = fGy + kLN;
-  float* fFxy = fFxx + kLN;
-  float* fFyx = fFxy + kLN;
-  float* fFyy = fFyx + kLN;
-  float* Pl = fFyy + kLN;  // [L][kLT][kLT]
-
-  const int nx = p.nx, ny = p.ny, L = p.lp.n;
-  const int ntx = (nx + kLT - 1) / kLT;
-  const int ty0 = (local / ntx) * kLT, tx0 = (local - (local / ntx) * ntx) * kLT;
-  const int ry0 = ty0 - kLH, rx0 = tx0 - kLH;
+// P_s of line s on the strip whose first output pixel is (y0, xs), into Pl[R][64] (lane columns).
+// EDGE: some derivative of the strip is one-sided (or a row or column lies off the image: the
+// values there are clamped reads that no output uses).  Otherwise every difference is central
+// and its halving is folded into the coefficients (exact).
+// XDEP: x-dependent spectrum, the line constants are those of the lane's column.
+template <int R, int ORDER, bool XDEP, bool EDGE>
+__device__ __forceinline__ void local_strip(const ProbDesc& p, int s, int y0, int xs, float* Pl) {
+  constexpr int N = R + 2 * kLH;
+  const int nx = p.nx, ny = p.ny;
+  const int lane = threadIdx.x & 63;
+  const int x = xs - kLH + lane;
+  const int xc = EDGE ? min(max(x, 0), nx - 1) : x;
   gptr<const float> X = G(p.X);
   gptr<const float> Y = G(p.Y);
+  float cw, ca, cb, cq;
+  if constexpr (XDEP) {
+    const float4 c = xcol_at(p, xc, s);
+    cw = c.x; ca = c.y; cb = c.z; cq = c.w;
+  } else {
+    cw = p.lp.w[s]; ca = p.lp.a[s]; cb = p.lp.b[s]; cq = p.lp.q[s];
+  }
+  const float ca2 = ca * 1.4426950408889634f;  // exp(-a x) = exp2(-a log2(e) x)
 
-  for (int s = 0; s < L; ++s) {
-    const float ws = p.lp.w[s], as = p.lp.a[s], bs = p.lp.b[s], qs = p.lp.q[s];
-    // level 4: I and A
-    FOR_LEVEL(kLH, {
-      float cw = ws;
-      float ca = as;
-      if constexpr (XDEP) {
-        const float4 c = xcol_at(p, x, s);
-        cw = c.x;
-        ca = c.y;
-      }
-      const float I = cw * expf(-ca * X[(size_t)y * nx + x]);
-      fI[o] = I;
-      fA[o] = sqrtf(I);
-    })
-    // level 3: D A
-    FOR_LEVEL(3, {
-      fDxA[o] = rdx(fA, ly, lx, x, nx);
-      fDyA[o] = rdy(fA, ly, lx, y, ny);
-    })
-    // level 2: Q and the transport products
-    FOR_LEVEL(2, {
-      const float I = fI[o];
-      float cb = bs;
-      if constexpr (XDEP) cb = xcol_at(p, x, s).z;
-      const float ux = cb * d_x(Y, y, x, nx);
-      const float uy = cb * d_y(Y, y, x, ny, nx);
-      fIx[o] = I * ux;
-      fIy[o] = I * uy;
-      fPxx[o] = I * ux * ux;
-      fPxy[o] = I * ux * uy;
-      fPyy[o] = I * uy * uy;
-      fQ[o] = (rdx(fDxA, ly, lx, x, nx) + rdy(fDyA, ly, lx, y, ny)) / fA[o];
-    })
-    // level 1: first derivatives of the second-order products, I D Q
-    FOR_LEVEL(1, {
-      fFxx[o] = rdx(fPxx, ly, lx, x, nx);
-      fFxy[o] = rdy(fPxy, ly, lx, y, ny);
-      fFyx[o] = rdx(fPxy, ly, lx, x, nx);
-      fFyy[o] = rdy(fPyy, ly, lx, y, ny);
-      const float I = fI[o];
-      fGx[o] = I * rdx(fQ, ly, lx, x, nx);
-      fGy[o] = I * rdy(fQ, ly, lx, y, ny);
-    })
-    // level 0: the closure
-    FOR_LEVEL(0, {
-      float P;
-      float cq = qs;
-      if constexpr (XDEP) cq = xcol_at(p, x, s).w;
-      if (order == kOrderTransportWkb1) {
-        const float t3 = rdx(fGx, ly, lx, x, nx) + rdy(fGy, ly, lx, y, ny);
-        P = G(p.e)[((size_t)s * ny + y) * nx + x] - cq * t3;
-      } else {
-      const float t1 = rdx(fIx, ly, lx, x, nx) + rdy(fIy, ly, lx, y, ny);
-      P = fI[o] - t1;
-      if (order >= 2) {
-        const float t2 = rdx(fFxx, ly, lx, x, nx) + rdx(fFxy, ly, lx, x, nx) +
-                         rdy(fFyx, ly, lx, y, ny) + rdy(fFyy, ly, lx, y, ny);
-        const float t3 = rdx(fGx, ly, lx, x, nx) + rdy(fGy, ly, lx, y, ny);
-        P += 0.5f * t2 - cq * t3;
-      }
-      }
-      Pl[(s * kLT + (ly - kLH)) * kLT + (lx - kLH)] = P;
-    })
+  // input row i is image row y0 - kLH + i
+  float Xv[N], Yv[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int y = y0 - kLH + i;
+    const int yc = EDGE ? min(max(y, 0), ny - 1) : y;
+    Xv[i] = ldg(X + yc * nx, (unsigned)xc);
+    if constexpr (ORDER != kOrderTransportWkb1) Yv[i] = ldg(Y + yc * nx, (unsigned)xc);
   }
 
+  const bool xfirst = x == 0, xlast = x == nx - 1;
+  const float sx = (xfirst || xlast) ? 1.f : 0.5f;
+  // D_x f; !EDGE: 2 D_x f
+  auto dx = [&](float f) {
+    float l = lane_left(f), r = lane_right(f);
+    if constexpr (EDGE) {
+      l = xfirst ? f : l;
+      r = xlast ? f : r;
+      return sx * (r - l);
+    }
+    return r - l;
+  };
+  // D_y at input row i from the values of rows i - 1, i, i + 1; !EDGE: 2 D_y
+  auto dy = [&](int i, float fm, float f0, float fp) {
+    if constexpr (EDGE) {
+      const int y = y0 - kLH + i;
+      const float t = y == 0 ? f0 : fm, b = y == ny - 1 ? f0 : fp;
+      return ((y == 0 || y == ny - 1) ? 1.f : 0.5f) * (b - t);
+    }
+    return fp - fm;
+  };
+  // coefficients of once, twice and four times differentiated terms
+  constexpr float k1 = EDGE ? 1.f : 0.5f, k2 = k1 * k1, k4 = k2 * k2;
+  const float cbg = cb * k1, cqg = cq * k4;
+  const float sw = __builtin_amdgcn_sqrtf(cw), ha2 = 0.5f * ca2;
+
+  float I[N], A[N], dyA[N], Q[N], GY[N], Ix[N], Iy[N], Pxx[N], Pxy[N], Pyy[N], dyP[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    // The closure's accuracy is I's: expf there.  In the pressure term, which is small against
+    // I, I and A come from the hardware exp2 (about one ulp); A by its own exponential, which
+    // underflows at half the exponent of I.
+    if constexpr (ORDER == kOrderTransportWkb1)
+      I[i] = cw * __builtin_amdgcn_exp2f(-ca2 * Xv[i]);
+    else
+      I[i] = cw * expf(-ca * Xv[i]);
+    if constexpr (ORDER >= 2) {
+      A[i] = sw * __builtin_amdgcn_exp2f(-ha2 * Xv[i]);
+      if (i >= 2) dyA[i - 1] = dy(i - 1, A[i - 2], A[i - 1], A[i]);
+    }
+    const int j = i - 2;
+    if constexpr (ORDER != kOrderTransportWkb1) {
+      if (j >= 2 && j < N - 2) {
+        const float ux = cbg * dx(Yv[j]), uy = cbg * dy(j, Yv[j - 1], Yv[j], Yv[j + 1]);
+        Ix[j] = I[j] * ux;
+        Iy[j] = I[j] * uy;
+        if constexpr (ORDER >= 2) {
+          Pxx[j] = Ix[j] * ux;
+          Pxy[j] = Ix[j] * uy;
+          Pyy[j] = Iy[j] * uy;
+        }
+      }
+    }
+    if constexpr (ORDER >= 2) {
+      if (j >= 2 && j < N - 2)
+        Q[j] = (dx(dx(A[j])) + dy(j, dyA[j - 1], dyA[j], dyA[j + 1])) * __builtin_amdgcn_rcpf(A[j]);
+      const int k = i - 3;
+      if (k >= 3 && k < N - 3) {
+        GY[k] = I[k] * dy(k, Q[k - 1], Q[k], Q[k + 1]);
+        if constexpr (ORDER == 2) dyP[k] = dy(k, Pyy[k - 1], Pyy[k], Pyy[k + 1]);
+      }
+    }
+    const int m = i - kLH;
+    if (m >= kLH && m < N - kLH) {
+      float P;
+      if constexpr (ORDER == kOrderTransportWkb1) {
+        const int y = y0 - kLH + m;
+        const int yc = EDGE ? min(max(y, 0), ny - 1) : y;
+        P = ldg(G((const float*)p.e) + ((size_t)s * ny + yc) * nx, (unsigned)xc);
+      } else {
+        P = I[m] - k1 * (dx(Ix[m]) + dy(m, Iy[m - 1], Iy[m], Iy[m + 1]));
+        if constexpr (ORDER >= 2) {
+          const float xy = dx(dy(m, Pxy[m - 1], Pxy[m], Pxy[m + 1]));
+          const float t2 = dx(dx(Pxx[m])) + 2.f * xy + dy(m, dyP[m - 1], dyP[m], dyP[m + 1]);
+          P += (0.5f * k2) * t2;
+        }
+      }
+      if constexpr (ORDER >= 2) {
+        const float t3 = dx(I[m] * dx(Q[m])) + dy(m, GY[m - 1], GY[m], GY[m + 1]);
+        P -= cqg * t3;
+      }
+      Pl[(m - kLH) * 64 + lane] = P;
+    }
+  }
+}
+
+template <int R, int ORDER, bool XDEP>
+__device__ __forceinline__ void local_body(const ProbDesc& p, int local, int mode) {
+  extern __shared__ float Pl[];  // [line][strip][R][64]
+  const int nx = p.nx, ny = p.ny, L = p.lp.n;
+  const int ns = local_strips(L);
+  const int ntx = (nx + ns * kLocalCols - 1) / (ns * kLocalCols);
+  const int y0 = (local / ntx) * R, tx0 = (local - (local / ntx) * ntx) * (ns * kLocalCols);
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  // the short strips (small images, latency) read the data before the closure; a wave sums the
+  // rows q = w + k nw, at most R of them
+  float dpre[R <= 8 ? R : 1];
+  if constexpr (R <= 8) {
+    if (mode == kLocalSplit) {
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        const int q = w + k * nw;
+        if (q < R * ns) {
+          const int r = q / ns, j = q - r * ns;
+          const int y = min(y0 + r, ny - 1);
+          const int x = min(max(tx0 + j * kLocalCols + lane - kLH, 0), nx - 1);
+          dpre[k] = ldg(G((const float*)p.d), (unsigned)(__mul24(y, nx) + x));
+        }
+      }
+    }
+  }
+  for (int u = w; u < L * ns; u += nw) {
+    const int s = u / ns, xs = tx0 + (u - s * ns) * kLocalCols;
+    if (xs >= nx) continue;
+    const bool inner = xs >= kLH && xs + kLocalCols + kLH <= nx && y0 >= kLH && y0 + R + kLH <= ny;
+    if (inner)
+      local_strip<R, ORDER, XDEP, false>(p, s, y0, xs, Pl + u * R * 64);
+    else
+      local_strip<R, ORDER, XDEP, true>(p, s, y0, xs, Pl + u * R * 64);
+  }
+  __syncthreads();
+
+  // sum over the lines, residual and split: one strip row per wave and step
   float se = 0.f, sd = 0.f;
-  for (int i = threadIdx.x; i < kLT * kLT; i += kLocalThreads) {
-    const int ly = i / kLT, lx = i - ly * kLT;
-    const int y = ty0 + ly, x = tx0 + lx;
-    if (y >= ny || x >= nx) continue;
-    const size_t pix = (size_t)y * nx + x;
+  auto sum_row = [&](int q, float dq) {
+    const int r = q / ns, j = q - r * ns;
+    const int y = y0 + r, x = tx0 + j * kLocalCols + lane - kLH;
+    if (lane < kLH || lane >= kLH + kLocalCols || y >= ny || x >= nx) return;
+    const unsigned pix = (unsigned)(__mul24(y, nx) + x);
+    const float* Pr = Pl + (j * R + r) * 64 + lane;
+    const int ls = ns * R * 64;  // line stride
     float P = 0.f, S = 0.f;
     for (int s = 0; s < L; ++s) {
-      const float v = Pl[s * kLT * kLT + i];
+      const float v = Pr[s * ls];
       P += v;
       S += fmaxf(v, 0.f);
     }
     if (mode == kLocalForward) {
-      G(p.out)[pix] = P;
+      stg(G(p.out), pix, P);
     } else if (mode == kLocalLines) {
-      for (int s = 0; s < L; ++s) G(p.e)[(size_t)s * nx * ny + pix] = Pl[s * kLT * kLT + i];
+      for (int s = 0; s < L; ++s) stg(G(p.e) + (size_t)s * nx * ny, pix, Pr[s * ls]);
     } else {
-      const float dv = G(p.d)[pix];
+      const float dv = R <= 8 ? dq : ldg(G((const float*)p.d), pix);
       const float e = dv - P;
       se += e * e;
       sd += dv * dv;
@@ -172,25 +224,32 @@ __device__ __forceinline__ void local_body(const ProbDesc& p, int local, int mod
       for (int s = 0; s < L; ++s) {
         float fw = p.lp.w[s];
         if constexpr (XDEP) fw = xcol_at(p, x, s).x;
-        const float share = hole ? fw : fmaxf(Pl[s * kLT * kLT + i], 0.f) * inv;
-        G(p.e)[(size_t)s * nx * ny + pix] = share * e;
+        const float share = hole ? fw : fmaxf(Pr[s * ls], 0.f) * inv;
+        stg(G(p.e) + (size_t)s * nx * ny, pix, share * e);
       }
     }
+  };
+  if constexpr (R <= 8) {
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+      if (w + k * nw < R * ns) sum_row(w + k * nw, dpre[k]);
+  } else {
+    for (int q = w; q < R * ns; q += nw) sum_row(q, 0.f);
   }
   if (mode == kLocalSplit && p.resid != nullptr) {
-    __shared__ float red[2][kLocalThreads / 64];
+    __shared__ float red[2][kMaxLines];
     se = wave_sum(se);
     sd = wave_sum(sd);
-    if ((threadIdx.x & 63) == 0) {
-      red[0][threadIdx.x >> 6] = se;
-      red[1][threadIdx.x >> 6] = sd;
+    if (lane == 0) {
+      red[0][w] = se;
+      red[1][w] = sd;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
       float te = 0.f, td = 0.f;
-      for (int w = 0; w < kLocalThreads / 64; ++w) {
-        te += red[0][w];
-        td += red[1][w];
+      for (int i = 0; i < nw; ++i) {
+        te += red[0][i];
+        td += red[1][i];
       }
       G(p.resid)[2 * local] = te;
       G(p.resid)[2 * local + 1] = td;
@@ -198,48 +257,44 @@ __device__ __forceinline__ void local_body(const ProbDesc& p, int local, int mod
   }
 }
 
-template <bool B>
-__global__ __launch_bounds__(kLocalThreads) void k_local(KArgs a,
-                                                         const ProbDesc* __restrict__ table,
-                                                         int order) {
-  EPR_DISPATCH(B, a, table, xcd_remap(blockIdx.x, gridDim.x), local_body<false>, a.mode, order);
-}
-// x-dependent spectrum
-template <bool B>
-__global__ __launch_bounds__(kLocalThreads) void k_local_x(KArgs a,
-                                                           const ProbDesc* __restrict__ table,
-                                                           int order) {
-  EPR_DISPATCH(B, a, table, xcd_remap(blockIdx.x, gridDim.x), local_body<true>, a.mode, order);
+template <bool B, int R, int ORDER, bool XDEP>
+__global__ __launch_bounds__(64 * kMaxLines) void k_local(KArgs a, const ProbDesc* __restrict__ table) {
+  EPR_DISPATCH(B, a, table, xcd_remap(blockIdx.x, gridDim.x), (local_body<R, ORDER, XDEP>), a.mode);
 }
 
-hipError_t launch_local(const KArgs& a, int total_blocks, size_t lds, hipStream_t s, int order) {
+template <int R, int ORDER>
+void launch_local_ro(const KArgs& a, int total_blocks, hipStream_t s, int lines) {
+  const int waves = lines * local_strips(lines);
+  const size_t lds = sizeof(float) * 64 * (size_t)R * waves;
+  const dim3 grid(total_blocks), block(64 * waves);
   if (a.xdep && a.table)
-    hipLaunchKernelGGL(k_local_x<true>, dim3(total_blocks), dim3(kLocalThreads), lds, s, a,
-                       a.table, order);
+    hipLaunchKernelGGL((k_local<true, R, ORDER, true>), grid, block, lds, s, a, a.table);
   else if (a.table)
-    hipLaunchKernelGGL(k_local<true>, dim3(total_blocks), dim3(kLocalThreads), lds, s, a, a.table,
-                       order);
+    hipLaunchKernelGGL((k_local<true, R, ORDER, false>), grid, block, lds, s, a, a.table);
   else if (a.p.xcol)
-    hipLaunchKernelGGL(k_local_x<false>, dim3(total_blocks), dim3(kLocalThreads), lds, s, a,
-                       a.table, order);
+    hipLaunchKernelGGL((k_local<false, R, ORDER, true>), grid, block, lds, s, a, a.table);
   else
-    hipLaunchKernelGGL(k_local<false>, dim3(total_blocks), dim3(kLocalThreads), lds, s, a, a.table,
-                       order);
-  return hipGetLastError();
+    hipLaunchKernelGGL((k_local<false, R, ORDER, false>), grid, block, lds, s, a, a.table);
 }
 
-size_t lds_local(int n_lines) {
-  return sizeof(float) * ((size_t)16 * kLN + (size_t)n_lines * kLT * kLT);
-}
-
-hipError_t set_local_attributes() {
-  const int mx = 160 * 1024 - 64;
-  for (const void* f : {(const void*)k_local<false>, (const void*)k_local<true>,
-                        (const void*)k_local_x<false>, (const void*)k_local_x<true>}) {
-    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, mx);
-    if (e != hipSuccess) return e;
+// lines: the line count of the launch's problems; rows: their rows per strip (ProbDesc::lrows).
+hipError_t launch_local(const KArgs& a, int total_blocks, hipStream_t s, int order, int lines,
+                        int rows) {
+  if (lines < 1 || lines > kMaxLines || (rows != 4 && rows != 8 && rows != 16)) return hipErrorInvalidValue;
+  if (rows == 4) {
+    if (order == 1) launch_local_ro<4, 1>(a, total_blocks, s, lines);
+    else if (order == 2) launch_local_ro<4, 2>(a, total_blocks, s, lines);
+    else launch_local_ro<4, 3>(a, total_blocks, s, lines);
+  } else if (rows == 8) {
+    if (order == 1) launch_local_ro<8, 1>(a, total_blocks, s, lines);
+    else if (order == 2) launch_local_ro<8, 2>(a, total_blocks, s, lines);
+    else launch_local_ro<8, 3>(a, total_blocks, s, lines);
+  } else {
+    if (order == 1) launch_local_ro<16, 1>(a, total_blocks, s, lines);
+    else if (order == 2) launch_local_ro<16, 2>(a, total_blocks, s, lines);
+    else launch_local_ro<16, 3>(a, total_blocks, s, lines);
   }
-  return hipSuccess;
+  return hipGetLastError();
 }
 
 }  // namespace epr
