@@ -45,8 +45,8 @@ UNIT = "2048^2 projections/s"
 HBM_PEAK_GBS = 8000.0
 STAGES = ("maxgrad", "splat", "local", "rowfft", "colfft", "rowinv", "vjp", "binsplit")
 KERNEL_SOURCE = {"maxgrad": "k_transport.hip", "splat": "k_transport.hip",
-                 "local": "k_local.hip", "rowfft": "k_spectral.hip",
-                 "colfft": "k_spectral.hip", "rowinv": "k_spectral.hip", "vjp": "k_vjp.hip",
+                 "local": "k_local.hip", "rowfft": "k_rowfft.hip",
+                 "colfft": "k_colfft.hip", "rowinv": "k_rowinv.hip", "vjp": "k_vjp.hip",
                  "binsplit": "k_transport.hip"}
 
 
@@ -132,7 +132,7 @@ def source_digest(stage):
     """SHA-256 of the kernel's translation unit and the device headers it includes."""
     csrc = os.path.join(ROOT, "paper_2601_22793_amd", "csrc")
     h = hashlib.sha256()
-    for f in (KERNEL_SOURCE[stage], "dev_common.h", "epr_internal.h", "fft_lds.h"):
+    for f in (KERNEL_SOURCE[stage], "dev_common.h", "epr_internal.h", "fft_lds.h", "spectral.h"):
         h.update(open(os.path.join(csrc, f), "rb").read())
     return h.hexdigest()
 

@@ -24,8 +24,8 @@ LIB = os.path.join(PKG, "libepr.so")
 # the library exports the C ABI (epr_*) only
 EXPORTS = "-Wl,--version-script=" + os.path.join(CSRC, "libepr.map")
 
-SOURCES = ["host_core.cpp", "api_ops.cpp", "api_solve.cpp", "api_batch.cpp", "api_tune.cpp", "k_transport.hip", "k_spectral.hip", "k_local.hip", "k_vjp.hip",
-           "k_regime.hip", "noalloc.hip"]
+SOURCES = ["host_core.cpp", "api_ops.cpp", "api_solve.cpp", "api_batch.cpp", "api_tune.cpp", "k_transport.hip",
+           "k_rowfft.hip", "k_colfft.hip", "k_rowinv.hip", "k_local.hip", "k_vjp.hip", "k_regime.hip", "noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -26,6 +26,7 @@ constexpr int kMaxStages = 16;
 constexpr int kMaxDim = 4096;
 constexpr int kColBlock = 4;     // complex columns per half-spectrum block
 constexpr int kRows = 4;         // rows per workgroup in the row passes
+static_assert(kRows == kColBlock, "the transform plans count kRows interleaved sequences");
 constexpr int kMaxgBlocks = 256; // workgroups of the max-gradient reduction per problem
 constexpr int kSplatThreads = 512;
 constexpr int kSplatTileX = 64;  // default splat tile (columns x rows)
@@ -241,7 +242,9 @@ hipError_t launch_vjp_transpose(const KArgs& a, int total_blocks, hipStream_t s,
 hipError_t noalloc_scratch_address(int device, void** out);
 hipError_t launch_twiddle_table(float2* out, int n, hipStream_t s);
 hipError_t set_transport_attributes();
-hipError_t set_spectral_attributes();
+hipError_t set_rowfft_attributes();
+hipError_t set_colfft_attributes();
+hipError_t set_rowinv_attributes();
 hipError_t set_vjp_attributes();
 
 }  // namespace epr

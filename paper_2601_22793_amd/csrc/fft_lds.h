@@ -85,6 +85,13 @@ __device__ __forceinline__ TwTable load_twiddles(int off, const FftPlan& plan, i
   return tt;
 }
 
+// Butterflies of radix R a thread holds in a stage of EMAX elements.  Radices 12 and 15 hold one
+// (30 complex values for two would double the registers of every kernel that has the stage):
+// the plans take them only where COUNT N / R <= NT (kernel_radices).
+constexpr int stage_bpt(int R, int NT, int EMAX) {
+  return R == 12 || R == 15 ? 1 : (EMAX / R + NT - 1) / NT;
+}
+
 // Forward R-point DFTs in registers (natural order in and out).
 template <int R>
 struct Dft;
@@ -196,6 +203,39 @@ struct Dft<9> {
   }
 };
 
+// R = A B with coprime A, B (Good-Thomas prime-factor mapping, no inner twiddles): input
+// n = (B n1 + A n2) mod R, output k with k = k1 mod A and k = k2 mod B, so that
+// W_R^(n k) = W_A^(n1 k1) W_B^(n2 k2) for the output order below: DFT_B over n2, DFT_A over n1.
+// EA = multiple of B that is 1 mod A, EB = multiple of A that is 1 mod B.
+template <int A, int B, int EA, int EB>
+struct DftCoprime {
+  static_assert(EA % B == 0 && EA % A == 1 && EB % A == 0 && EB % B == 1, "index mapping");
+  __device__ __forceinline__ static void run(float2* u) {
+    float2 a[A][B];
+#pragma unroll
+    for (int n1 = 0; n1 < A; ++n1) {
+#pragma unroll
+      for (int n2 = 0; n2 < B; ++n2) a[n1][n2] = u[(B * n1 + A * n2) % (A * B)];
+      Dft<B>::run(a[n1]);
+    }
+#pragma unroll
+    for (int k2 = 0; k2 < B; ++k2) {
+      float2 b[A];
+#pragma unroll
+      for (int n1 = 0; n1 < A; ++n1) b[n1] = a[n1][k2];
+      Dft<A>::run(b);
+#pragma unroll
+      for (int k1 = 0; k1 < A; ++k1) u[(EA * k1 + EB * k2) % (A * B)] = b[k1];
+    }
+  }
+};
+template <>
+struct Dft<6> : DftCoprime<2, 3, 3, 4> {};
+template <>
+struct Dft<10> : DftCoprime<2, 5, 5, 6> {};
+template <>
+struct Dft<12> : DftCoprime<3, 4, 4, 9> {};
+
 template <>
 struct Dft<15> {
   // 15 = 3 x 5 with coprime factors (Good-Thomas prime-factor mapping, no inner twiddles):
@@ -255,7 +295,7 @@ struct Dft<16> {
 };
 
 // Multiply u[r] by W_N^(r t), r = 1..R-1 (r t < N).  Radix <= 5: powers of W^t by repeated
-// products.  Radix 9 and 15: see below.  Radix 8 and 16: two table reads, W^t and W^(4t), and W^(4a+b) = W^(4a) W^b with
+// products.  Radix 6, 9, 10, 12 and 15: see below.  Radix 8 and 16: two table reads, W^t and W^(4t), and W^(4a+b) = W^(4a) W^b with
 // W^2, W^3, W^8, W^12 formed by products, so each factor carries at most two roundings beyond
 // the table's.  (Relative error of a 2048-point transform in FP32: about 1.1e-7, against
 // 7.5e-8 with one table read per factor.)
@@ -269,10 +309,10 @@ __device__ __forceinline__ void apply_twiddles(float2 (&u)[R], const TwTable& tw
       u[r] = cmul(u[r], w);
       if (r + 1 < R) w = cmul(w, w1);
     }
-  } else if constexpr (R == 9 || R == 15) {
-    // R = A B with B = 3 or 5: W^(B a + b) = W^(B a) W^b, powers of W^t and W^(B t) (two table
-    // reads) by at most three products
-    constexpr int B = R == 9 ? 3 : 5, A = R / B;
+  } else if constexpr (R != 8 && R != 16) {
+    // R = A B with A = 2 or 3 and B = 3, 4 or 5: W^(B a + b) = W^(B a) W^b, powers of W^t and
+    // W^(B t) (two table reads) by at most three products
+    constexpr int B = R % 5 == 0 ? 5 : R == 12 ? 4 : 3, A = R / B;
     float2 wb[B];
     wb[1] = w1;
 #pragma unroll
@@ -322,7 +362,7 @@ __device__ __forceinline__ void fft_stage(int boff, int n_rt, int p_rt, float in
   float2* buf = lds_f2() + boff;
   const int N = NC ? NC : n_rt;
   const int p = PC ? PC : p_rt;
-  constexpr int BPT = (EMAX / R + NT - 1) / NT;
+  constexpr int BPT = stage_bpt(R, NT, EMAX);
   const int T = N / R;
   const int total = COUNT * T;
   float2 u[BPT][R];
@@ -420,6 +460,11 @@ __device__ __forceinline__ void fft_stage_radix(int boff, int N, int R, int p, T
     case 4: fft_stage_call<4, COUNT, NT, EMAX, TAG, FIRST>(boff, N, p, inv_p, tw); break;
     case 2: fft_stage_call<2, COUNT, NT, EMAX, TAG, FIRST>(boff, N, p, inv_p, tw); break;
     case 5: fft_stage_call<5, COUNT, NT, EMAX, TAG, FIRST>(boff, N, p, inv_p, tw); break;
+    case 6: fft_stage_call<6, COUNT, NT, EMAX, TAG, FIRST>(boff, N, p, inv_p, tw); break;
+    case 9: fft_stage_call<9, COUNT, NT, EMAX, TAG, FIRST>(boff, N, p, inv_p, tw); break;
+    case 10: fft_stage_call<10, COUNT, NT, EMAX, TAG, FIRST>(boff, N, p, inv_p, tw); break;
+    case 12: fft_stage_call<12, COUNT, NT, EMAX, TAG, FIRST>(boff, N, p, inv_p, tw); break;
+    case 15: fft_stage_call<15, COUNT, NT, EMAX, TAG, FIRST>(boff, N, p, inv_p, tw); break;
     default: fft_stage_call<3, COUNT, NT, EMAX, TAG, FIRST>(boff, N, p, inv_p, tw); break;
   }
 }
@@ -556,7 +601,7 @@ __device__ __forceinline__ void fft_fused_filter_stage(int boff, int n_rt, TwTab
                                                                 ColumnFilter filt) {
   float2* buf = lds_f2() + boff;
   const int N = NC ? NC : n_rt;
-  constexpr int BPT = (EMAX / R + NT - 1) / NT;
+  constexpr int BPT = stage_bpt(R, NT, EMAX);
   const int T = N / R;  // = p of the last forward stage
   const int total = COUNT * T;
   float2 u[BPT][R];
@@ -686,6 +731,11 @@ __device__ __forceinline__ bool fft_filter_ifft_lds(int boff, const FftPlan& pla
     case 4: fft_fused_filter_stage<4, COUNT, NT, EMAX, TAG>(boff, N, tw, filt); break;
     case 2: fft_fused_filter_stage<2, COUNT, NT, EMAX, TAG>(boff, N, tw, filt); break;
     case 5: fft_fused_filter_stage<5, COUNT, NT, EMAX, TAG>(boff, N, tw, filt); break;
+    case 6: fft_fused_filter_stage<6, COUNT, NT, EMAX, TAG>(boff, N, tw, filt); break;
+    case 9: fft_fused_filter_stage<9, COUNT, NT, EMAX, TAG>(boff, N, tw, filt); break;
+    case 10: fft_fused_filter_stage<10, COUNT, NT, EMAX, TAG>(boff, N, tw, filt); break;
+    case 12: fft_fused_filter_stage<12, COUNT, NT, EMAX, TAG>(boff, N, tw, filt); break;
+    case 15: fft_fused_filter_stage<15, COUNT, NT, EMAX, TAG>(boff, N, tw, filt); break;
     default: fft_fused_filter_stage<3, COUNT, NT, EMAX, TAG>(boff, N, tw, filt); break;
   }
   fft_lds_stages<COUNT, NT, EMAX, TAG>(boff, plan, tw, 1, plan.nst, last, true);

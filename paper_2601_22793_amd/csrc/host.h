@@ -46,6 +46,7 @@ extern thread_local std::string g_create_error;
 // Radix sequence for n (product of 2, 3, 5): radix 16 first, then the rest of the power of
 // two as 8 / 4 / 2, then 5s and 3s.  Returns the number of stages, or -1.
 int factorize(int n, int* radix, int cap);
+int kernel_radices(int n, int nt, int* radix, int cap);
 bool smooth235(int n);
 
 struct Twiddles {
@@ -100,6 +101,8 @@ struct epr_ctx {
   BatchPlan batch;
   std::string last_error;
   std::map<int, Twiddles> tw;           // length -> W_n table
+  struct Radices { int nst, radix[epr::kMaxStages]; };
+  std::map<std::pair<int, int>, Radices> radices;  // (length, threads) -> radix sequence
   DevBuf ws;                            // single-problem workspace
   DevBuf hist;                          // residual history (256 floats)
   DevBuf batch_ws;                      // batched workspace
@@ -234,7 +237,7 @@ int ensure(epr_ctx* h, DevBuf& b, size_t bytes);
 hipEvent_t take_event(epr_ctx* h);
 int fold_events(epr_ctx* h, std::vector<epr_ctx::EvPair>& v, bool recycle);
 const float2* twiddles(epr_ctx* h, int n, int* status);
-int make_plan(epr_ctx* h, int n, int table_n, int stride, FftPlan* out,
+int make_plan(epr_ctx* h, int n, int nt, int table_n, int stride, FftPlan* out,
               const float2* table = nullptr);
 int check_geometry(epr_ctx* h, const epr_geometry* g);
 int check_spectrum_header(epr_ctx* h, const epr_spectrum* s);

@@ -32,6 +32,48 @@ int factorize(int n, int* radix, int cap) {
   return k <= cap ? k : -1;
 }
 
+// Radix sequence the kernels run for a length without a compile-time sequence: the cheapest
+// product of the radices they have, by vector instructions per element.  A stage costs a fixed
+// part (index arithmetic, LDS traffic and two barriers), its butterfly and, after the first
+// stage, its twiddles.  Composite radices halve the stages of lengths with few factors of two
+// (1215 = 15 9 9 instead of 5 3 3 3 3 3): a 15-iteration solve of 1215 x 1500 with 4 lines went
+// from 2364 to 1942 us, one of 1080 x 1200 with 4 lines (20 iterations) from 2450 to 2159 us.
+// Radices 15 and 12 need their butterflies to fit one per thread (nt threads, kRows = kColBlock
+// interleaved sequences).  n must be a product of 2, 3 and 5.  Returns the number of stages (0
+// for n = 1).
+int kernel_radices(int n, int nt, int* radix, int cap) {
+  struct Cost { int r; float dft; };
+  static const Cost kCost[] = {{16, 11.f}, {15, 12.f}, {12, 8.7f}, {10, 9.2f}, {9, 12.f},
+                               {8, 7.f},   {6, 6.7f},  {5, 7.f},   {4, 4.f},   {3, 4.7f},
+                               {2, 2.f}};
+  constexpr float kStage = 18.f, kTwiddle = 8.f;
+  std::map<int, std::pair<float, int>> best;  // divisor d -> cost of the radices after n / d, next
+  std::function<float(int)> solve = [&](int d) -> float {
+    if (d == 1) return 0.f;
+    auto it = best.find(d);
+    if (it != best.end()) return it->second.first;
+    float bc = 1e30f;
+    int br = 0;
+    for (const Cost& c : kCost) {
+      if (d % c.r || ((c.r == 15 || c.r == 12) && kRows * (n / c.r) > nt)) continue;
+      const float v = kStage + c.dft + kTwiddle * (c.r - 1) / c.r + solve(d / c.r);
+      if (v < bc - 1e-3f) {
+        bc = v;
+        br = c.r;
+      }
+    }
+    best[d] = {bc, br};
+    return bc;
+  };
+  solve(n);
+  int k = 0;
+  for (int d = n; d > 1; d /= best[d].second) {
+    if (k >= cap) return -1;
+    radix[k++] = best[d].second;
+  }
+  return k;
+}
+
 bool smooth235(int n) {
   int r[kMaxStages * 2];
   return factorize(n, r, kMaxStages * 2) >= 0;
@@ -105,12 +147,19 @@ const float2* twiddles(epr_ctx* h, int n, int* status) {
   return tw.dev;
 }
 
-// `table`: a W_table_n table the caller provides (else the handle's cached one).
-int make_plan(epr_ctx* h, int n, int table_n, int stride, FftPlan* out,
+// nt: threads of the kernels that run the plan; `table`: a W_table_n table the caller provides (else the handle's cached one).
+int make_plan(epr_ctx* h, int n, int nt, int table_n, int stride, FftPlan* out,
               const float2* table) {
   out->n = n;
   out->tw_stride = stride;
-  out->nst = factorize(n, out->radix, kMaxStages);
+  auto it = h->radices.find({n, nt});
+  if (it == h->radices.end()) {
+    epr_ctx::Radices r{};
+    r.nst = smooth235(n) ? kernel_radices(n, nt, r.radix, kMaxStages) : -1;
+    it = h->radices.emplace(std::make_pair(n, nt), r).first;
+  }
+  out->nst = it->second.nst;
+  std::memcpy(out->radix, it->second.radix, sizeof out->radix);
   if (out->nst < 0) return h->fail(EPR_ERR_SHAPE, "FFT length %d is not a product of 2, 3, 5", n);
   int st = EPR_OK;
   out->tw = table ? table : twiddles(h, table_n, &st);
@@ -464,9 +513,9 @@ int fill_desc(epr_ctx* h, const epr_geometry& g, const LineParams& lp, char* bas
     p->maxg = reinterpret_cast<float*>(base + w.e + w.spec);
     p->resid = reinterpret_cast<float*>(base + w.e + w.spec + w.maxg);
   }
-  int st = make_plan(h, g.nx / 2, g.nx, 2, &p->row, row_tab);
+  int st = make_plan(h, g.nx / 2, spectral_threads(*p), g.nx, 2, &p->row, row_tab);
   if (st) return st;
-  st = make_plan(h, g.ny, g.ny, 1, &p->col, col_tab);
+  st = make_plan(h, g.ny, spectral_threads(*p), g.ny, 1, &p->col, col_tab);
   if (st) return st;
   auto rv = h->fft_row_var.find(g.nx / 2), cv = h->fft_col_var.find(g.ny);
   p->row.variant = rv == h->fft_row_var.end() ? 0 : rv->second;
@@ -772,7 +821,9 @@ int epr_create(epr_handle* out, int device) {
   // Opt the kernels into the large dynamic LDS they may need.  A runtime that does not
   // support the attribute leaves the default; a launch needing more then fails and reports.
   (void)set_transport_attributes();
-  (void)set_spectral_attributes();
+  (void)set_rowfft_attributes();
+  (void)set_colfft_attributes();
+  (void)set_rowinv_attributes();
   (void)set_vjp_attributes();
   (void)set_regime_attributes();
   (void)hipGetLastError();

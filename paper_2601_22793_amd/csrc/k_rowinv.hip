@@ -1,0 +1,264 @@
+// Row inverse pass: inverse row real FFT with the fused update and single-thickness projection
+// (Methods 4.4, Eq. 7).
+#include <hip/hip_runtime.h>
+
+#include "spectral.h"
+
+namespace epr {
+
+// ---------------------------------------------------------------------------------------------
+// Row inverse pass: per block of kRows rows, for every line: inverse real FFT of the filtered
+// half spectrum -> dI_s; then either write dI_s (precondition mode) or accumulate the
+// projection of I_s + omega dI_s onto one thickness (solve mode) and write tau.
+//   * The block's 4 x 4 tiles of a line are copied verbatim to LDS by direct global->LDS loads;
+//     the next line's copy streams in while the current line is transformed (the transform
+//     reads its twiddles from LDS, so no other global load waits behind the copy).
+//   * The thread's pixels, their thickness and their projection sums stay in registers.
+// ---------------------------------------------------------------------------------------------
+template <int NT>
+__device__ __forceinline__ void fetch_row_tiles(gptr<const float2> sp, float2* dst, int nblk,
+                                                int ny, int y0) {
+  // 16-byte chunk q of the block: tile blk = q / 8, row r = (q / 2) % 4, columns 2 (q % 2) + {0,1}
+  const int nq = nblk * 8;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float4* d4 = reinterpret_cast<float4*>(dst);
+  for (int base = wave * 64; base < nq; base += NT) {
+    const int q = base + lane;
+    if (q < nq) {
+      const int blk = q >> 3, r = (q >> 1) & 3;
+      const int y = min(y0 + r, ny - 1);  // rows past the image repeat the last row
+      gptr<const char> src = (gptr<const char>)sp + (unsigned)(((blk * ny + y) * 2 + (q & 1)) * 16);
+      __builtin_amdgcn_global_load_lds((const gvoid_t*)src, (lvoid_t*)(d4 + base), 16, 0, 0);
+    }
+  }
+}
+
+// XDEP: x-dependent spectrum, the update and projection constants are read per column.
+// BLK (with XDEP): block-wise preconditioner.  Each line has p.nbp filtered spectra, one per
+// preconditioner block b (block 0 at p.spec, block b >= 1 in p.spec_blk); the row
+// inverse transforms each of them and blends them per column with the interpolation weights
+// lambda_b(x) (p.xblk[x] = {b0, t}: lambda_b0 = 1 - t, lambda_(b0+1) = t, 0 otherwise) before
+// the update.
+template <int NT, bool SOLVE, bool XDEP, bool BLK = false>
+__device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
+  using SC = SizeClass<NT>;
+  extern __shared__ float2 buf[];
+  const int nx = p.nx, ny = p.ny, M = nx >> 1;
+  const int y0 = local * kRows;
+  const int L = p.lp.n;
+  const int tid = threadIdx.x;
+  const int nin = p.nblk * kColBlock * kRows;  // complex values of one line's tiles
+  const size_t line_elems = (size_t)p.nblk * ny * kColBlock;
+  float2* raw = buf;        // the line's tiles as copied: [block][row][column]
+  float2* F = buf + nin;    // transform buffer
+  const TwTable tw = load_twiddles(nin + kRows * lds_rows(M), p.row, tid, NT);
+  const float2 w1 = G(p.row_tw)[1];
+  gptr<const float2> spec = G((const float2*)p.spec);
+  fetch_row_tiles<NT>(spec, raw, p.nblk, ny, y0);
+
+  // the thread's pixels: row r, column x = tid + j NT (k = r * kPerRow + j)
+  constexpr int kPerRow = SC::kMaxNx / NT;
+  // live[j]: the wave has columns of chunk j inside the row (wave-uniform; narrow images in a
+  // size class leave whole chunks empty, which are then skipped)
+  bool live[kPerRow];
+#pragma unroll
+  for (int j = 0; j < kPerRow; ++j)
+    live[j] = __builtin_amdgcn_readfirstlane((tid & ~63) + j * NT) < nx;
+  float tv[SC::kPix], acc[SC::kPix];
+#pragma unroll
+  for (int k = 0; k < SC::kPix; ++k) {
+    const int r = k / kPerRow, x = min(tid + (k % kPerRow) * NT, nx - 1);
+    const int y = min(y0 + r, ny - 1);
+    tv[k] = 0.f;
+    if constexpr (SOLVE)
+      if (live[k % kPerRow]) tv[k] = ldg(G((const float*)p.tau), (unsigned)(__mul24(y, nx) + x));
+    acc[k] = 0.f;
+  }
+  const float odd_sign = (tid & 1) ? -1.f : 1.f;  // NT is even: x has the parity of tid
+  const RowPix<NT> pix(tid);
+  // sum of every update the thread applies: finite exactly when each of them is (the floor
+  // of the update would otherwise hide a NaN)
+  float chk = 0.f;
+  // transform units: one per line, or one per (line, preconditioner block), block fastest
+  const int nb = BLK ? p.nbp : 1;
+  const int nunit = L * nb;
+  float dacc[BLK ? SC::kPix : 1];
+#pragma unroll
+  for (int k = 0; k < (BLK ? SC::kPix : 1); ++k) dacc[k] = 0.f;
+
+  for (int un = 0; un < nunit; ++un) {
+    const int s = BLK ? un / nb : un;
+    const int bk = BLK ? un - s * nb : 0;
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's copies of unit un have landed
+    __syncthreads();                // ... and everyone's; unit un-1 is no longer read
+    // Z[k] = E_k + i O_k, E_k = (X_k + conj X_{M-k})/2, O_k = (X_k - conj X_{M-k})/2 W^-k;
+    // store conj(Z) so that a forward FFT followed by conjugation inverts it.
+    // W_nx^(M-k) = -conj(W_nx^k).
+    const int half = M >> 1;
+    for (int i = tid; i < (half + 1) * kRows; i += NT) {
+      const int k = i / kRows, r = i - k * kRows;
+      // tile position of frequency k in row r: (k / 4) * 16 + r * 4 + k % 4
+      const float2 xk = raw[((k >> 2) << 4) | (r << 2) | (k & 3)];
+      const float2 xm = raw[(((M - k) >> 2) << 4) | (r << 2) | ((M - k) & 3)];
+      const float2 wk = half_tw(tw, w1, k);
+      {
+        const float2 xmc = cconj(xm);
+        const float2 E = make_float2(0.5f * (xk.x + xmc.x), 0.5f * (xk.y + xmc.y));
+        const float2 D = make_float2(0.5f * (xk.x - xmc.x), 0.5f * (xk.y - xmc.y));
+        const float2 O = cmul(D, cconj(wk));
+        const float2 Z = make_float2(E.x - O.y, E.y + O.x);
+        F[lds_index<kRows>(k, r)] = cconj(Z);
+      }
+      if (k != 0 && 2 * k != M) {
+        const float2 xkc = cconj(xk);
+        const float2 E = make_float2(0.5f * (xm.x + xkc.x), 0.5f * (xm.y + xkc.y));
+        const float2 D = make_float2(0.5f * (xm.x - xkc.x), 0.5f * (xm.y - xkc.y));
+        const float2 O = cmul(D, make_float2(-wk.x, -wk.y));  // conj(W^(M-k)) = -W^k
+        const float2 Z = make_float2(E.x - O.y, E.y + O.x);
+        F[lds_index<kRows>(M - k, r)] = cconj(Z);
+      }
+    }
+    __syncthreads();  // the tiles are consumed: unit un+1 streams in during the transform
+    if (un + 1 < nunit) {
+      const int s1 = BLK ? (un + 1) / nb : un + 1, b1 = BLK ? (un + 1) - s1 * nb : 0;
+      gptr<const float2> sb = b1 == 0 ? spec : G((const float2*)p.spec_blk) + (size_t)(b1 - 1) * p.spec_set;
+      fetch_row_tiles<NT>(sb + (size_t)s1 * line_elems, raw, p.nblk, ny, y0);
+    }
+    fft_lds<kRows, NT, SC::kRowEmax, SOLVE ? (BLK ? 5 : 3) : 4>(nin, p.row, tw);
+
+    const float* fb = reinterpret_cast<const float*>(F);
+    if constexpr (BLK) {
+      // blend this block's output into the line's update; the update follows the last block
+#pragma unroll
+      for (int k = 0; k < SC::kPix; ++k) {
+        const int r = k / kPerRow, x = tid + (k % kPerRow) * NT;
+        if (live[k % kPerRow] && x < nx) {
+          const float2 bt = ldg(G(p.xblk), (unsigned)x);
+          const int b0 = (int)bt.x;
+          const float lam = bk == b0 ? 1.f - bt.y : (bk == b0 + 1 ? bt.y : 0.f);
+          dacc[k] = fmaf(lam, odd_sign * fb[pix.at(r, k % kPerRow)], dacc[k]);
+        }
+      }
+      if (bk + 1 < nb) continue;
+    }
+    if constexpr (SOLVE) {
+      // The projection takes ln(max(I_s + omega dI_s, 1e-6 w_s) / w_s) as
+      // ln(max(exp(-a_s tau) + (omega / w_s) dI_s, 1e-6)): the same value, but formed without
+      // the product w_s (1 / w_s), whose float32 rounding (about 1e-7, different in every
+      // column of an x-dependent spectrum) would otherwise enter every iteration as a thickness
+      // offset of that size over mu_s.  exp and ln through the hardware base-2 transcendentals
+      // (v_exp_f32 / v_log_f32): the ratio stays a normal number (>= 1e-6), where both are
+      // accurate to about one ulp.
+      const float la2 = p.lp.a[s] * 1.4426950408889634f;
+      const float mws_ln2 = p.lp.mw[s] * 0.69314718055994531f;
+      const float om = p.relax, om_w = p.relax * p.lp.inv_w[s];
+#pragma unroll
+      for (int k = 0; k < SC::kPix; ++k) {
+        const int r = k / kPerRow, x = tid + (k % kPerRow) * NT;
+        if (live[k % kPerRow] && x < nx) {
+          // conj of the transform output: the odd (imaginary) samples change sign
+          float dI;
+          if constexpr (BLK) {
+            dI = dacc[k];
+            dacc[k] = 0.f;
+          } else {
+            dI = odd_sign * fb[pix.at(r, k % kPerRow)];
+          }
+          chk += dI;
+          if constexpr (XDEP) {
+            const float4 c = xcol_at(p, x, s), q = xproj_at(p, x, s);
+            const float g = __builtin_amdgcn_exp2f(-(c.y * 1.4426950408889634f) * tv[k]);
+            const float r = fmaxf(fmaf(om * q.y, dI, g), 1e-6f);
+            acc[k] += (q.x * 0.69314718055994531f) * __builtin_amdgcn_logf(r);
+          } else {
+            const float g = __builtin_amdgcn_exp2f(-la2 * tv[k]);
+            const float r = fmaxf(fmaf(om_w, dI, g), 1e-6f);
+            acc[k] += mws_ln2 * __builtin_amdgcn_logf(r);
+          }
+        }
+      }
+    } else {
+      gptr<float> o = G(p.out) + (size_t)s * nx * ny;
+#pragma unroll
+      for (int k = 0; k < SC::kPix; ++k) {
+        const int r = k / kPerRow, x = tid + (k % kPerRow) * NT, y = y0 + r;
+        if (live[k % kPerRow] && x < nx && y < ny)
+          stg(o, (unsigned)(__mul24(y, nx) + x), odd_sign * fb[pix.at(r, k % kPerRow)]);
+      }
+    }
+  }
+
+  if constexpr (SOLVE) {
+    const float inv_den = p.lp.inv_den, pc = p.lp.phase_coef;
+    bool bad = !(fabsf(chk) <= 3.40282347e38f);
+#pragma unroll
+    for (int k = 0; k < SC::kPix; ++k) {
+      const int r = k / kPerRow, x = tid + (k % kPerRow) * NT, y = y0 + r;
+      if (live[k % kPerRow] && x < nx && y < ny) {
+        float id = inv_den;
+        if constexpr (XDEP) id = ldg(G(p.xden), (unsigned)x);
+        const float t = -acc[k] * id;
+        bad = bad || !(fabsf(t) <= 3.40282347e38f);
+        stg(G(p.tau), (unsigned)(__mul24(y, nx) + x), t);
+        if (p.phase_out) stg(G(p.phase_out), (unsigned)(__mul24(y, nx) + x), pc * t);
+      }
+    }
+    // one vector store per wave that met a non-finite value (every writer stores 1)
+    if (__any(bad) && (tid & 63) == 0 && p.status != nullptr) G(p.status)[0] = 1u;
+  }
+}
+
+// solve and precondition modes are separate kernels: each is register-allocated for its own path
+template <bool B, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_rowinv(
+    KArgs a, const ProbDesc* __restrict__ table) {
+  EPR_DISPATCH(B, a, table, xcd_remap(blockIdx.x, gridDim.x), (rowinv_body<NT, true, false>), 0);
+}
+template <bool B, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_rowinv_x(
+    KArgs a, const ProbDesc* __restrict__ table) {
+  EPR_DISPATCH(B, a, table, xcd_remap(blockIdx.x, gridDim.x), (rowinv_body<NT, true, true>), 0);
+}
+// x-dependent spectrum with the block-wise preconditioner
+template <int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_rowinv_xb(
+    KArgs a, const ProbDesc* __restrict__ table) {
+  EPR_DISPATCH(false, a, table, xcd_remap(blockIdx.x, gridDim.x),
+               (rowinv_body<NT, true, true, true>), 0);
+}
+template <bool B, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_rowinv_pre(
+    KArgs a, const ProbDesc* __restrict__ table) {
+  EPR_DISPATCH(B, a, table, xcd_remap(blockIdx.x, gridDim.x), (rowinv_body<NT, false, false>), 0);
+}
+
+// single-problem kernels (the block-wise row inverse)
+#define EPR_LAUNCH_X(K, a, grid, nt, lds, s)                                                  \
+  do {                                                                                       \
+    if (nt == 512)                                                                           \
+      hipLaunchKernelGGL((K<512>), dim3(grid), dim3(512), lds, s, a, a.table);              \
+    else                                                                                     \
+      hipLaunchKernelGGL((K<1024>), dim3(grid), dim3(1024), lds, s, a, a.table);            \
+  } while (0)
+
+hipError_t launch_rowinv(const KArgs& a, int total_blocks, size_t lds, hipStream_t s, int nt) {
+  const bool x = a.table ? a.xdep != 0 : a.p.xcol != nullptr;
+  if (a.mode == kRowInvSolve && !a.table && a.p.xcol && a.p.nbp > 0)
+    EPR_LAUNCH_X(k_rowinv_xb, a, total_blocks, nt, lds, s);
+  else if (a.mode == kRowInvSolve && x)
+    EPR_LAUNCH_SC(k_rowinv_x, a, total_blocks, nt, lds, s);
+  else if (a.mode == kRowInvSolve)
+    EPR_LAUNCH_SC(k_rowinv, a, total_blocks, nt, lds, s);
+  else
+    EPR_LAUNCH_SC(k_rowinv_pre, a, total_blocks, nt, lds, s);
+  return hipGetLastError();
+}
+
+
+hipError_t set_rowinv_attributes() {
+  const void* const fns[] = {EPR_SC_FNS(k_rowinv), EPR_SC_FNS(k_rowinv_pre), EPR_SC_FNS(k_rowinv_x),
+                             (const void*)k_rowinv_xb<512>, (const void*)k_rowinv_xb<1024>};
+  return allow_dynamic_lds(fns);
+}
+
+}  // namespace epr
