@@ -105,7 +105,7 @@ struct ProbDesc {
   int os;             // oversampling factor f: ny x nx is the internal grid, d is the detector
                       // image of (ny/f) x (nx/f) pixels, each the mean of f x f internal pixels
   // x-dependent effective spectrum (null: the LineParams constants hold for every column):
-  // xcol[(x * L + s) * 2] = {w, a, b, q}, xcol[(x * L + s) * 2 + 1] = {mw, 1/w, floor, 0} of
+  // xcol[2 s nx + x] = {w, a, b, q}, xcol[(2 s + 1) nx + x] = {mw, 1/w, floor, 0} of
   // line s at column x, xden[x] = 1 / sum_s w mu^2 there.
   const float4* xcol;
   const float* xden;

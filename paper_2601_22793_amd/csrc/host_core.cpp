@@ -428,9 +428,9 @@ XTable xspec_table(const epr_geometry& g, const epr_spectrum& s, const epr_spect
       const double mu = 2.0 * k * beta;
       const double eps = g.distance_m / k / p2;
       const double b = -eps * k * delta;
-      t.col[((size_t)x * L + i) * 2] =
+      t.col[(size_t)(2 * i) * nx + x] =
           make_float4((float)w, (float)mu, (float)b, (float)(0.25 * eps * eps));
-      t.col[((size_t)x * L + i) * 2 + 1] =
+      t.col[(size_t)(2 * i + 1) * nx + x] =
           make_float4((float)(w * mu), (float)(1.0 / w), (float)(1e-6 * w), 0.f);
       den += w * mu * mu;
       amean[i] += eps * delta / (2.0 * beta);

@@ -153,28 +153,31 @@ __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
       const float mws_ln2 = p.lp.mw[s] * 0.69314718055994531f;
       const float om = p.relax, om_w = p.relax * p.lp.inv_w[s];
 #pragma unroll
-      for (int k = 0; k < SC::kPix; ++k) {
-        const int r = k / kPerRow, x = tid + (k % kPerRow) * NT;
-        if (live[k % kPerRow] && x < nx) {
+      for (int j = 0; j < kPerRow; ++j) {
+        const int x = tid + j * NT;
+        if (!live[j] || x >= nx) continue;
+        float c_a2 = la2, c_ow = om_w, c_mw = mws_ln2;
+        if constexpr (XDEP) {  // the column's constants, once for its kRows pixels
+          const float4 c = xcol_at(p, x, s), q = xproj_at(p, x, s);
+          c_a2 = c.y * 1.4426950408889634f;
+          c_ow = om * q.y;
+          c_mw = q.x * 0.69314718055994531f;
+        }
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+          const int k = r * kPerRow + j;
           // conj of the transform output: the odd (imaginary) samples change sign
           float dI;
           if constexpr (BLK) {
             dI = dacc[k];
             dacc[k] = 0.f;
           } else {
-            dI = odd_sign * fb[pix.at(r, k % kPerRow)];
+            dI = odd_sign * fb[pix.at(r, j)];
           }
           chk += dI;
-          if constexpr (XDEP) {
-            const float4 c = xcol_at(p, x, s), q = xproj_at(p, x, s);
-            const float g = __builtin_amdgcn_exp2f(-(c.y * 1.4426950408889634f) * tv[k]);
-            const float r = fmaxf(fmaf(om * q.y, dI, g), 1e-6f);
-            acc[k] += (q.x * 0.69314718055994531f) * __builtin_amdgcn_logf(r);
-          } else {
-            const float g = __builtin_amdgcn_exp2f(-la2 * tv[k]);
-            const float r = fmaxf(fmaf(om_w, dI, g), 1e-6f);
-            acc[k] += mws_ln2 * __builtin_amdgcn_logf(r);
-          }
+          const float g = __builtin_amdgcn_exp2f(-c_a2 * tv[k]);
+          const float v = fmaxf(fmaf(c_ow, dI, g), 1e-6f);
+          acc[k] += c_mw * __builtin_amdgcn_logf(v);
         }
       }
     } else {
