@@ -123,6 +123,28 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+// Maxima over aligned groups of 8, 16 and all 64 lanes with DPP row modes (no LDS round trip, as a
+// shuffle takes).  Every lane must be active; the result is in every lane of the group.
+#define EPR_DPP_MAX(v, ctrl) \
+  fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false)))
+__device__ __forceinline__ float lane8_max(float v) {
+  v = EPR_DPP_MAX(v, 0xB1);         // quad_perm [1, 0, 3, 2]
+  v = EPR_DPP_MAX(v, 0x4E);         // quad_perm [2, 3, 0, 1]
+  return EPR_DPP_MAX(v, 0x141);     // row_half_mirror
+}
+__device__ __forceinline__ float lane16_max(float v) {
+  return EPR_DPP_MAX(lane8_max(v), 0x140);  // row_mirror
+}
+__device__ __forceinline__ float lane64_max(float v) {
+  const int m = __float_as_int(lane16_max(v));
+  const float a = fmaxf(__int_as_float(__builtin_amdgcn_readlane(m, 0)),
+                        __int_as_float(__builtin_amdgcn_readlane(m, 16)));
+  const float b = fmaxf(__int_as_float(__builtin_amdgcn_readlane(m, 32)),
+                        __int_as_float(__builtin_amdgcn_readlane(m, 48)));
+  return fmaxf(a, b);
+}
+#undef EPR_DPP_MAX
+
 // Halo (in pixels, per axis) that covers every source whose bilinear footprint can reach a
 // tile: H = floor(max |u|) + 1, with max |u| = max_s |b_s| * max |D Y| (rounding is monotone,
 // so this bounds every per-source shift computed as b_s * D Y).  Capped at the image size.

@@ -28,6 +28,14 @@ constexpr int kColBlock = 4;     // complex columns per half-spectrum block
 constexpr int kRows = 4;         // rows per workgroup in the row passes
 static_assert(kRows == kColBlock, "the transform plans count kRows interleaved sequences");
 constexpr int kMaxgBlocks = 256; // workgroups of the max-gradient reduction per problem
+constexpr int kSegCols = 32;     // columns of a segment of the max-gradient maxima
+__host__ __device__ inline int seg_cols(int nx) { return (nx + kSegCols - 1) / kSegCols; }
+// Row band of the segment maxima that holds row y: the max-gradient workgroup's band (band k is
+// rows k ny / kMaxgBlocks up to the next band's), or the row itself for at most kMaxgBlocks rows.
+// min(ny, kMaxgBlocks) seg_cols(nx) float4 never exceed the spectra's L nblk ny kColBlock float2.
+__host__ __device__ inline int seg_band(int y, int ny) {
+  return ny <= kMaxgBlocks ? y : ((y + 1) * kMaxgBlocks - 1) / ny;
+}
 constexpr int kSplatThreads = 512;
 constexpr int kSplatTileX = 64;  // default splat tile (columns x rows)
 constexpr int kSplatTileY = 32;
@@ -95,6 +103,9 @@ struct ProbDesc {
   float* tau;         // solve state, in/out
   float* phase_out;   // optional
   float* maxg;        // [kMaxgBlocks][3]
+  float4* segs;       // [seg_band(ny - 1) + 1][seg_cols(nx)] signed maxima of D Y per row band and
+                      // segment of kSegCols columns.  Lies in the storage of spec, which holds
+                      // nothing between a row inverse and the next row pass (the splat's place)
   float* resid;       // residual partial sums [splat blocks][2] (may be null)
   unsigned* status;   // set to 1 when an update meets a NaN or an infinity (may be null)
   FftPlan row;        // length nx/2 (twiddles of length nx, stride 2)

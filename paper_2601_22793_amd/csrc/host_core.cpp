@@ -510,6 +510,7 @@ int fill_desc(epr_ctx* h, const epr_geometry& g, const LineParams& lp, char* bas
   if (base) {
     p->e = reinterpret_cast<float*>(base);
     p->spec = reinterpret_cast<float2*>(base + w.e);
+    p->segs = reinterpret_cast<float4*>(base + w.e);
     p->maxg = reinterpret_cast<float*>(base + w.e + w.spec);
     p->resid = reinterpret_cast<float*>(base + w.e + w.spec + w.maxg);
   }

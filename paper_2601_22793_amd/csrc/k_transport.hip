@@ -11,7 +11,10 @@
 namespace epr {
 
 // ---------------------------------------------------------------------------------------------
-// max |D_x Y|, max |D_y Y| and min X over the image: one partial triple per workgroup.
+// max |D_x Y|, max |D_y Y| and min X over the image, one partial triple per workgroup (a band of
+// rows), and the largest positive and negative parts of both differences on every segment of
+// kSegCols columns of the band (p.segs): from the former the splat bounds how far away a
+// tile's sources can lie, from the latter how far those it can actually meet are displaced.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMaxgThreads = 1024;  // (a band is a few rows: many loads in flight per workgroup)
 
@@ -19,71 +22,115 @@ __device__ __forceinline__ void maxgrad_body(const ProbDesc& p, int local, int) 
   const int nx = p.nx, ny = p.ny;
   gptr<const float> Y = G(p.Y);
   gptr<const float> X = G(p.X);
-  float mx = 0.f, my = 0.f, mn = INFINITY;
+  const int nseg = seg_cols(nx);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int kWaves = kMaxgThreads / 64;
+  // {max D_x Y, max -D_x Y, max D_y Y, max -D_y Y}, at least 0, per segment, as float bits (whose
+  // order is that of the values for non-negative floats); NaNs drop out of the maxima
+  __shared__ unsigned seg[kMaxDim / kSegCols * 4];
+  __shared__ float red[kWaves];
+  for (int i = tid; i < nseg * 4; i += kMaxgThreads) seg[i] = 0u;
+  __syncthreads();
+  float mn = INFINITY;
   // each workgroup takes one band of whole rows, so that the rows above and below a pixel are
   // read by the same workgroup (from its caches) rather than fetched again by others
   const int y0 = (int)(((long long)local * ny) / kMaxgBlocks);
   const int y1 = (int)(((long long)(local + 1) * ny) / kMaxgBlocks);
+  // the lanes of an aligned group of 8 (four pixels each) or 16 (one each) lie in one segment
+  auto deposit = [&](int x, int group, float xp, float xm, float yp, float ym) {
+    if (group == 8) {
+      xp = lane8_max(xp);
+      xm = lane8_max(xm);
+      yp = lane8_max(yp);
+      ym = lane8_max(ym);
+    } else {
+      xp = lane16_max(xp);
+      xm = lane16_max(xm);
+      yp = lane16_max(yp);
+      ym = lane16_max(ym);
+    }
+    if ((lane & (group - 1)) == 0 && x < nx) {
+      unsigned* s = seg + (x / kSegCols) * 4;
+      atomicMax(s, __float_as_uint(xp));
+      atomicMax(s + 1, __float_as_uint(xm));
+      atomicMax(s + 2, __float_as_uint(yp));
+      atomicMax(s + 3, __float_as_uint(ym));
+    }
+  };
   if ((nx & 3) == 0 && ((reinterpret_cast<uintptr_t>(p.Y) | reinterpret_cast<uintptr_t>(p.X)) & 15) == 0) {
-    // 4 consecutive pixels per item: three float4 loads (rows y-1, y, y+1) and the two
-    // neighbours of the segment; clamping reproduces the one-sided edge differences
-    const int nq = nx >> 2;
-    const int n = nq * (y1 - y0);
-    for (int i = threadIdx.x; i < n; i += kMaxgThreads) {
-      const int yb = i / nq;
-      const int y = y0 + yb, x = (i - yb * nq) << 2;
-      const int yl = max(y - 1, 0), yh = min(y + 1, ny - 1);
-      const float sy = (yh - yl == 2) ? 0.5f : 1.f;
-      const float4 c = ldg((gptr<const float4>)Y, (unsigned)(__mul24(y, nx) + x) >> 2);
-      const float4 u = ldg((gptr<const float4>)Y, (unsigned)(__mul24(yl, nx) + x) >> 2);
-      const float4 d = ldg((gptr<const float4>)Y, (unsigned)(__mul24(yh, nx) + x) >> 2);
-      const float4 xv = ldg((gptr<const float4>)X, (unsigned)(__mul24(y, nx) + x) >> 2);
-      const float l = ldg(Y, (unsigned)(__mul24(y, nx) + max(x - 1, 0)));
-      const float r = ldg(Y, (unsigned)(__mul24(y, nx) + min(x + 4, nx - 1)));
-      // x differences: the first/last pixel of the row use one-sided differences
-      const float g0 = (x == 0) ? c.y - c.x : 0.5f * (c.y - l);
-      const float g1 = 0.5f * (c.z - c.x);
-      const float g2 = 0.5f * (c.w - c.y);
-      const float g3 = (x + 4 == nx) ? c.w - c.z : 0.5f * (r - c.z);
-      mx = fmaxf(mx, fmaxf(fmaxf(fabsf(g0), fabsf(g1)), fmaxf(fabsf(g2), fabsf(g3))));
-      const float h0 = fabsf(sy * (d.x - u.x)), h1 = fabsf(sy * (d.y - u.y));
-      const float h2 = fabsf(sy * (d.z - u.z)), h3 = fabsf(sy * (d.w - u.w));
-      my = fmaxf(my, fmaxf(fmaxf(h0, h1), fmaxf(h2, h3)));
-      mn = fminf(mn, fminf(fminf(xv.x, xv.y), fminf(xv.z, xv.w)));
+    // 4 consecutive pixels per lane: three float4 loads (rows y-1, y, y+1) and the two
+    // neighbours of the segment; clamping reproduces the one-sided edge differences.  A wave
+    // takes 256 columns of every (kWaves / nc)-th row of the band and reduces over lanes once.
+    const int nc = (nx + 255) >> 8;
+    static_assert((kMaxDim + 255) / 256 <= kWaves, "a column block per wave");
+    const int ng = kWaves / nc, g = w / nc;
+    const int x = ((w - g * nc) << 8) + 4 * lane;
+    float xp = 0.f, xm = 0.f, yp = 0.f, ym = 0.f;
+    if (g < ng && x < nx) {
+#pragma unroll 2
+      for (int y = y0 + g; y < y1; y += ng) {
+        const int yl = max(y - 1, 0), yh = min(y + 1, ny - 1);
+        const float sy = (yh - yl == 2) ? 0.5f : 1.f;
+        const float4 c = ldg((gptr<const float4>)Y, (unsigned)(__mul24(y, nx) + x) >> 2);
+        const float4 u = ldg((gptr<const float4>)Y, (unsigned)(__mul24(yl, nx) + x) >> 2);
+        const float4 d = ldg((gptr<const float4>)Y, (unsigned)(__mul24(yh, nx) + x) >> 2);
+        const float4 xv = ldg((gptr<const float4>)X, (unsigned)(__mul24(y, nx) + x) >> 2);
+        const float l = ldg(Y, (unsigned)(__mul24(y, nx) + max(x - 1, 0)));
+        const float r = ldg(Y, (unsigned)(__mul24(y, nx) + min(x + 4, nx - 1)));
+        // x differences: the first/last pixel of the row use one-sided differences
+        const float g0 = (x == 0) ? c.y - c.x : 0.5f * (c.y - l);
+        const float g1 = 0.5f * (c.z - c.x);
+        const float g2 = 0.5f * (c.w - c.y);
+        const float g3 = (x + 4 == nx) ? c.w - c.z : 0.5f * (r - c.z);
+        const float h0 = sy * (d.x - u.x), h1 = sy * (d.y - u.y);
+        const float h2 = sy * (d.z - u.z), h3 = sy * (d.w - u.w);
+        xp = fmaxf(xp, fmaxf(fmaxf(g0, g1), fmaxf(g2, g3)));
+        xm = fmaxf(xm, fmaxf(fmaxf(-g0, -g1), fmaxf(-g2, -g3)));
+        yp = fmaxf(yp, fmaxf(fmaxf(h0, h1), fmaxf(h2, h3)));
+        ym = fmaxf(ym, fmaxf(fmaxf(-h0, -h1), fmaxf(-h2, -h3)));
+        mn = fminf(mn, fminf(fminf(xv.x, xv.y), fminf(xv.z, xv.w)));
+      }
     }
+    if (g < ng) deposit(x, 8, xp, xm, yp, ym);
   } else {
-    const int n = nx * (y1 - y0);
-    for (int i = threadIdx.x; i < n; i += kMaxgThreads) {
-      const int yb = i / nx;
-      const int y = y0 + yb, x = i - yb * nx;
-      mx = fmaxf(mx, fabsf(d_x(Y, y, x, nx)));
-      my = fmaxf(my, fabsf(d_y(Y, y, x, ny, nx)));
-      mn = fminf(mn, ldg(X, (unsigned)(__mul24(y, nx) + x)));
+    const int nc = (nx + 63) >> 6;
+    for (int t = w; t < nc * (y1 - y0); t += kWaves) {
+      const int yb = t / nc;
+      const int y = y0 + yb, x = ((t - yb * nc) << 6) + lane;
+      float gx = 0.f, gy = 0.f;
+      if (x < nx) {
+        gx = d_x(Y, y, x, nx);
+        gy = d_y(Y, y, x, ny, nx);
+        mn = fminf(mn, ldg(X, (unsigned)(__mul24(y, nx) + x)));
+      }
+      deposit(x, 16, fmaxf(gx, 0.f), fmaxf(-gx, 0.f), fmaxf(gy, 0.f), fmaxf(-gy, 0.f));
     }
   }
-  constexpr int kWaves = kMaxgThreads / 64;
-  __shared__ float red[3][kWaves];
-  mx = wave_max(mx);
-  my = wave_max(my);
   mn = -wave_max(-mn);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    red[0][w] = mx;
-    red[1][w] = my;
-    red[2][w] = mn;
-  }
+  if (lane == 0) red[w] = mn;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    float a = red[0][0], b = red[1][0], c = red[2][0];
-    for (int k = 1; k < kWaves; ++k) {
-      a = fmaxf(a, red[0][k]);
-      b = fmaxf(b, red[1][k]);
-      c = fminf(c, red[2][k]);
+  if (w == 0) {
+    float a = 0.f, b = 0.f, c = lane < kWaves ? red[lane] : INFINITY;
+    for (int i = lane; i < nseg; i += 64) {
+      float4 s;
+      s.x = __uint_as_float(seg[4 * i]);
+      s.y = __uint_as_float(seg[4 * i + 1]);
+      s.z = __uint_as_float(seg[4 * i + 2]);
+      s.w = __uint_as_float(seg[4 * i + 3]);
+      a = fmaxf(a, fmaxf(s.x, s.y));
+      b = fmaxf(b, fmaxf(s.z, s.w));
+      if (y1 > y0) stg(G(p.segs), (unsigned)(seg_band(y0, ny) * nseg + i), s);
     }
-    gptr<float> mg = G(p.maxg);
-    mg[3 * local] = a;
-    mg[3 * local + 1] = b;
-    mg[3 * local + 2] = c;
+    a = wave_max(a);
+    b = wave_max(b);
+    c = -wave_max(-c);
+    if (lane == 0) {
+      gptr<float> mg = G(p.maxg);
+      mg[3 * local] = a;
+      mg[3 * local + 1] = b;
+      mg[3 * local + 2] = c;
+    }
   }
 }
 
@@ -95,7 +142,7 @@ __global__ __launch_bounds__(kMaxgThreads) void k_maxgrad(KArgs a, const ProbDes
 // ---------------------------------------------------------------------------------------------
 // Splat.  A workgroup owns a TY x TX tile of the detector and accumulates, for every line, the
 // bilinear deposits of all sources whose mapped footprint can reach the tile (sources within
-// the halo H derived on the device from the max-gradient partials) in LDS with LDS atomics.
+// the halo derived on the device from the max-gradient partials and segments) in LDS with LDS atomics.
 // Each detector pixel is written by exactly one workgroup: no global atomics.
 //   forward mode: out = sum_s P_s
 //   split mode  : e = d - sum_s P_s, e_s = pi_s e with pi_s = max(P_s,0)/sum max(P_s',0)
@@ -161,7 +208,7 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
   // without per-corner bounds checks; the border is discarded.
   extern __shared__ unsigned int acc_u[];
   float* acc_f = reinterpret_cast<float*>(acc_u);
-  __shared__ float red[3][kSplatThreads / 64];
+  __shared__ float red[2][kSplatThreads / 64];
   const int nx = p.nx, ny = p.ny;
   const int TX = p.splat_tx, TY = p.splat_ty;
   const int ptile = (TX + 2) * (TY + 2);
@@ -179,41 +226,101 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
     lb[s] = s < L ? p.lp.b[s] : 0.f;
   }
 
-  // halo and minimum of X from the max-gradient partials
-  float gx = 0.f, gy = 0.f, xmin = INFINITY;
-  gptr<const float> mg = G(p.maxg);
-  for (int i = tid; i < kMaxgBlocks; i += kSplatThreads) {
-    gx = fmaxf(gx, ldg(mg, (unsigned)(3 * i)));
-    gy = fmaxf(gy, ldg(mg, (unsigned)(3 * i + 1)));
-    xmin = fminf(xmin, ldg(mg, (unsigned)(3 * i + 2)));
+  // Halo of the tile and minimum of X.  The segment maxima around the tile (kGuessX columns and
+  // kGuessY rows away, one entry per thread) bound the shifts of the sources there, by sign; the
+  // partials' maximum bounds every shift of the image.  When the latter keeps all sources that
+  // reach the tile within the former's surroundings, the former gives the tile's halo: a tile
+  // away from the steepest edges reads few sources that it does not need.  All in the first
+  // kScanWaves waves, with one barrier.
+  // 2048 x 2048, 8 lines, shifts up to 6 pixels: splat 84 -> 66 us a launch (73 us of it by the
+  // halo and this prologue, the rest by reading the detector data before the source loop);
+  // max-gradient 7.5 -> 8.3 us for the signed segment maxima.
+  constexpr int kGuessX = kSegCols, kGuessY = kSplatTileY / 2;
+  constexpr int kScanWaves = kMaxgBlocks / 64;
+  static_assert(kScanWaves * 64 <= kSplatThreads, "one partial per thread");
+  __shared__ float4 red4[kScanWaves][2];
+  const int nseg = seg_cols(nx);
+  gptr<const float4> segs = G((const float4*)p.segs);
+  const int gs0 = max(tx0 - kGuessX, 0) / kSegCols;
+  const int gns = min(tx0 + TX - 1 + kGuessX, nx - 1) / kSegCols - gs0 + 1;
+  const int gb0 = seg_band(max(ty0 - kGuessY, 0), ny);
+  const int gn = gns * (seg_band(min(ty0 + TY - 1 + kGuessY, ny - 1), ny) - gb0 + 1);
+  if (tid < kMaxgBlocks) {
+    gptr<const float> mg = G(p.maxg);
+    float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (tid < gn) m = ldg(segs, (unsigned)((gb0 + tid / gns) * nseg + gs0 + tid % gns));
+    float gx = ldg(mg, (unsigned)(3 * tid)), gy = ldg(mg, (unsigned)(3 * tid + 1));
+    float xmin = ldg(mg, (unsigned)(3 * tid + 2));
+    m.x = lane64_max(m.x);
+    m.y = lane64_max(m.y);
+    m.z = lane64_max(m.z);
+    m.w = lane64_max(m.w);
+    gx = lane64_max(gx);
+    gy = lane64_max(gy);
+    xmin = -lane64_max(-xmin);
+    if ((tid & 63) == 0) {
+      red4[tid >> 6][0] = m;
+      red4[tid >> 6][1] = make_float4(gx, gy, xmin, 0.f);
+    }
   }
-  gx = wave_max(gx);
-  gy = wave_max(gy);
-  xmin = -wave_max(-xmin);
-  if ((tid & 63) == 0) {
-    red[0][tid >> 6] = gx;
-    red[1][tid >> 6] = gy;
-    red[2][tid >> 6] = xmin;
+  {
+    // clear the accumulators, 16 bytes at a time
+    const int n = L * ptile;
+    uint4* a4 = reinterpret_cast<uint4*>(acc_u);
+    for (int i = tid; i < (n >> 2); i += kSplatThreads) a4[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < (n & 3)) acc_u[(n & ~3) + tid] = 0u;
   }
-  for (int i = tid; i < L * ptile; i += kSplatThreads) acc_u[i] = 0u;
   __syncthreads();
-  gx = red[0][0];
-  gy = red[1][0];
-  xmin = red[2][0];
+  float4 sm = red4[0][0], gm = red4[0][1];
 #pragma unroll
-  for (int w = 1; w < kSplatThreads / 64; ++w) {
-    gx = fmaxf(gx, red[0][w]);
-    gy = fmaxf(gy, red[1][w]);
-    xmin = fminf(xmin, red[2][w]);
+  for (int w = 1; w < kScanWaves; ++w) {
+    const float4 a = red4[w][0], b = red4[w][1];
+    sm = make_float4(fmaxf(sm.x, a.x), fmaxf(sm.y, a.y), fmaxf(sm.z, a.z), fmaxf(sm.w, a.w));
+    gm.x = fmaxf(gm.x, b.x);
+    gm.y = fmaxf(gm.y, b.y);
+    gm.z = fminf(gm.z, b.z);
   }
-  const int hx = halo_from(p.lp.b_absmax, gx);
-  const int hy = halo_from(p.lp.b_absmax, gy);
+  const float xmin = gm.z;
+  const int hx = halo_from(p.lp.b_absmax, gm.x);
+  const int hy = halo_from(p.lp.b_absmax, gm.y);
+  if (hx > kGuessX || hy > kGuessY || gn > kMaxgBlocks) {
+    // sources from further away (or too many entries above): the segments the image's halo spans
+    const int s0 = max(tx0 - hx, 0) / kSegCols, s1 = min(tx0 + TX - 1 + hx, nx - 1) / kSegCols;
+    const int b0 = seg_band(max(ty0 - hy, 0), ny), b1 = seg_band(min(ty0 + TY - 1 + hy, ny - 1), ny);
+    const int ns = s1 - s0 + 1;
+    float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = tid; i < ns * (b1 - b0 + 1); i += kSplatThreads) {
+      const float4 v = ldg(segs, (unsigned)((b0 + i / ns) * nseg + s0 + i % ns));
+      m = make_float4(fmaxf(m.x, v.x), fmaxf(m.y, v.y), fmaxf(m.z, v.z), fmaxf(m.w, v.w));
+    }
+    __shared__ float4 redw[kSplatThreads / 64];
+    m = make_float4(lane64_max(m.x), lane64_max(m.y), lane64_max(m.z), lane64_max(m.w));
+    if ((tid & 63) == 0) redw[tid >> 6] = m;
+    __syncthreads();
+    sm = redw[0];
+#pragma unroll
+    for (int w = 1; w < kSplatThreads / 64; ++w) {
+      const float4 a = redw[w];
+      sm = make_float4(fmaxf(sm.x, a.x), fmaxf(sm.y, a.y), fmaxf(sm.z, a.z), fmaxf(sm.w, a.w));
+    }
+  }
+  // Sources to the left (above) reach the tile with positive shifts, to the right (below) with
+  // negative ones; one pixel of halo each way at least (halo_from).  The shifts are b_s D Y with
+  // every b_s of one sign: positive for a phase map, negative for a thickness.
+  bool bneg = XDEP;
+#pragma unroll
+  for (int s = 0; s < NL; ++s) bneg = bneg || lb[s] < 0.f;
+  const int hxl = halo_from(p.lp.b_absmax, bneg ? sm.y : sm.x);
+  const int hxr = halo_from(p.lp.b_absmax, bneg ? sm.x : sm.y);
+  const int hyt = halo_from(p.lp.b_absmax, bneg ? sm.w : sm.z);
+  const int hyb = halo_from(p.lp.b_absmax, bneg ? sm.z : sm.w);
 
   // Fixed-point accumulation (integer LDS atomics: several times the throughput of float
   // atomics, and order-independent).  Every source deposits at most its intensity, which is at
-  // most w_s exp(-a_s min X), into one pixel, and at most (2hx+2)(2hy+2) sources reach a pixel,
-  // so with scale_s = 2^30 / (w_s exp(-a_s min X) window) no sum can exceed 2^30.
-  const float window = (float)(2 * hx + 2) * (float)(2 * hy + 2);
+  // most w_s exp(-a_s min X), into one pixel, and at most (hxl+hxr+2)(hyt+hyb+2) sources reach it,
+  // so with scale_s = 4.29e9 / (w_s exp(-a_s min X) window) no sum exceeds 4.29e9, and with up to
+  // one unit more per deposit (rounding) none reaches 2^32.
+  const float window = (float)(hxl + hxr + 2) * (float)(hyt + hyb + 2);
   float scale[NL], inv_scale[NL];
   bool fixed = window <= kFixedWindowMax;
 #pragma unroll
@@ -221,7 +328,7 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
     // (x-dependent: the largest w_s with the a_s bound that maximises exp(-a_s min X))
     const float la2b = (XDEP && xmin < 0.f && s < L) ? p.lp.a_hi[s] * 1.4426950408889634f : la2[s];
     const float imax = lw[s] * __builtin_amdgcn_exp2f(-la2b * xmin);
-    scale[s] = 1073741824.f / (imax * window);
+    scale[s] = 4.29e9f / (imax * window);
     inv_scale[s] = 1.f / scale[s];
     if (s < L && !(scale[s] > 0.f && scale[s] < 3.0e38f && inv_scale[s] > 0.f)) fixed = false;
   }
@@ -230,12 +337,24 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
 #pragma unroll
   for (int s = 0; s < NL; ++s) lws[s] = fixed ? lw[s] * scale[s] : lw[s];
 
-  const int sy0 = max(ty0 - hy, 0), sy1 = min(ty0 + TY - 1 + hy, ny - 1);
-  const int sx0 = max(tx0 - hx, 0), sx1 = min(tx0 + TX - 1 + hx, nx - 1);
+  const int sy0 = max(ty0 - hyt, 0), sy1 = min(ty0 + TY - 1 + hyb, ny - 1);
+  const int sx0 = max(tx0 - hxl, 0), sx1 = min(tx0 + TX - 1 + hxr, nx - 1);
   const int wsrc = sx1 - sx0 + 1;
   const int nsrc = wsrc * (sy1 - sy0 + 1);
   gptr<const float> X = G(p.X);
   gptr<const float> Y = G(p.Y);
+
+  // the default tile's detector data, read before the source loop that hides their latency
+  constexpr int kPre = kSplatTileX * kSplatTileY / kSplatThreads;
+  float dpre[kPre];
+  if (mode == kSplatSplit && TX == kSplatTileX && TY == kSplatTileY) {
+#pragma unroll
+    for (int k = 0; k < kPre; ++k) {
+      const int i = tid + k * kSplatThreads;
+      const int y = min(ty0 + i / kSplatTileX, ny - 1), x = min(tx0 + i % kSplatTileX, nx - 1);
+      dpre[k] = ldg(G((const float*)p.d), (unsigned)(__mul24(y, nx) + x));
+    }
+  }
 
   // The source loop and the read-back, specialised for the common case (every line of the
   // bound in use, fixed-point accumulation, the default tile): no per-line tests are left in it.
@@ -330,10 +449,10 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
     }
     __syncthreads();
 
-    for (int i = tid; i < TXk * TYk; i += kSplatThreads) {
+    auto read_back = [&](int i, float dq) {
       const int ly = i / TXk, lx = i - ly * TXk;
       const int y = ty0 + ly, x = tx0 + lx;
-      if (y >= ny || x >= nx) continue;
+      if (y >= ny || x >= nx) return;
       const unsigned pix = (unsigned)(__mul24(y, nx) + x);
       const int o = (ly + 1) * PXk + lx + 1;
       float Pv[NL];
@@ -355,7 +474,7 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
         for (int s = 0; s < NL; ++s)
           if (FULL || s < L) stg(G(p.e), (unsigned)(s * plane) + pix, Pv[s]);
       } else {
-        const float dv = ldg(G((const float*)p.d), pix);
+        const float dv = FULL ? dq : ldg(G((const float*)p.d), pix);
         const float e = dv - P;
         se += e * e;
         sd += dv * dv;
@@ -371,6 +490,12 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
           }
         }
       }
+    };
+    if constexpr (FULL) {
+#pragma unroll
+      for (int k = 0; k < kPre; ++k) read_back(tid + k * kSplatThreads, dpre[k]);
+    } else {
+      for (int i = tid; i < TXk * TYk; i += kSplatThreads) read_back(i, 0.f);
     }
   };
   const bool inner = sy0 >= 1 && sy1 <= ny - 2 && sx0 >= 1 && sx1 <= nx - 2;
