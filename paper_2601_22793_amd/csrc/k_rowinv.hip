@@ -2,6 +2,8 @@
 // (Methods 4.4, Eq. 7).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "spectral.h"
 
 namespace epr {
@@ -74,6 +76,15 @@ __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
       if (live[k % kPerRow]) tv[k] = ldg(G((const float*)p.tau), (unsigned)(__mul24(y, nx) + x));
     acc[k] = 0.f;
   }
+  // some a_s tau of the wave's pixels leaves the range of the update's difference form
+  bool thick = false;
+  if constexpr (SOLVE) {
+    float amax = 0.f, tmax = 0.f;
+    for (int s = 0; s < L; ++s) amax = fmaxf(amax, p.lp.a_hi[s]);
+#pragma unroll
+    for (int k = 0; k < SC::kPix; ++k) tmax = fmaxf(tmax, tv[k]);
+    thick = __any(!(amax * tmax <= 8.f));
+  }
   const float odd_sign = (tid & 1) ? -1.f : 1.f;  // NT is even: x has the parity of tid
   const RowPix<NT> pix(tid);
   // sum of every update the thread applies: finite exactly when each of them is (the floor
@@ -142,44 +153,64 @@ __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
       if (bk + 1 < nb) continue;
     }
     if constexpr (SOLVE) {
-      // The projection takes ln(max(I_s + omega dI_s, 1e-6 w_s) / w_s) as
-      // ln(max(exp(-a_s tau) + (omega / w_s) dI_s, 1e-6)): the same value, but formed without
-      // the product w_s (1 / w_s), whose float32 rounding (about 1e-7, different in every
-      // column of an x-dependent spectrum) would otherwise enter every iteration as a thickness
-      // offset of that size over mu_s.  exp and ln through the hardware base-2 transcendentals
-      // (v_exp_f32 / v_log_f32): the ratio stays a normal number (>= 1e-6), where both are
-      // accurate to about one ulp.
+      // The projection sums w_s mu_s ln(max(I_s + omega dI_s, 1e-6 w_s) / w_s).  With
+      // E = exp(a_s tau) and z = (omega / w_s) dI_s that logarithm is
+      //   -a_s tau + ln(max(1 + z E, 1e-6 E)),
+      // and since sum_s w_s mu_s a_s = 1 / inv_den, tau itself leaves the sum: the new thickness is
+      // tau - inv_den sum_s w_s mu_s ln(max(1 + z E, 1e-6 E)).  Near convergence the logarithm is
+      // small, so its rounding and that of E count for little, where exp(-a_s tau) and the
+      // logarithm of it, rounded, would give tau back to a few 1e-7 only in every iteration
+      // (errors of whole solves: halved for multi-pixel shifts, a fifth for the local closure).
+      // exp and ln through the hardware base-2 transcendentals (v_exp_f32 / v_log_f32, about one
+      // ulp).  Waves that hold a pixel with a_s tau > 8 (transmission below 3e-4, where a new
+      // thickness far from tau would cancel) take -ln(max(exp(-a_s tau) + z, 1e-6)) as it stands.
       const float la2 = p.lp.a[s] * 1.4426950408889634f;
       const float mws_ln2 = p.lp.mw[s] * 0.69314718055994531f;
       const float om = p.relax, om_w = p.relax * p.lp.inv_w[s];
+      auto update = [&](auto difference) {
 #pragma unroll
-      for (int j = 0; j < kPerRow; ++j) {
-        const int x = tid + j * NT;
-        if (!live[j] || x >= nx) continue;
-        float c_a2 = la2, c_ow = om_w, c_mw = mws_ln2;
-        if constexpr (XDEP) {  // the column's constants, once for its kRows pixels
-          const float4 c = xcol_at(p, x, s), q = xproj_at(p, x, s);
-          c_a2 = c.y * 1.4426950408889634f;
-          c_ow = om * q.y;
-          c_mw = q.x * 0.69314718055994531f;
-        }
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-          const int k = r * kPerRow + j;
+        for (int j = 0; j < kPerRow; ++j) {
+          const int x = tid + j * NT;
+          if (!live[j] || x >= nx) continue;
           // conj of the transform output: the odd (imaginary) samples change sign
-          float dI;
-          if constexpr (BLK) {
-            dI = dacc[k];
-            dacc[k] = 0.f;
-          } else {
-            dI = odd_sign * fb[pix.at(r, j)];
+          float c_a2 = la2, c_z = om_w * odd_sign, c_mw = mws_ln2;
+          if constexpr (XDEP) {  // the column's constants, once for its kRows pixels
+            const float4 c = xcol_at(p, x, s), q = xproj_at(p, x, s);
+            c_a2 = c.y * 1.4426950408889634f;
+            c_z = BLK ? om * q.y : om * q.y * odd_sign;
+            c_mw = q.x * 0.69314718055994531f;
           }
-          chk += dI;
-          const float g = __builtin_amdgcn_exp2f(-c_a2 * tv[k]);
-          const float v = fmaxf(fmaf(c_ow, dI, g), 1e-6f);
-          acc[k] += c_mw * __builtin_amdgcn_logf(v);
+#pragma unroll
+          for (int r = 0; r < kRows; ++r) {
+            const int k = r * kPerRow + j;
+            float v;
+            if constexpr (BLK) {
+              v = dacc[k];
+              dacc[k] = 0.f;
+            } else {
+              v = fb[pix.at(r, j)];
+            }
+            chk += v;
+            const float t2 = c_a2 * tv[k], z = c_z * v;
+            float l;
+            if constexpr (decltype(difference)::value) {
+              const float E = __builtin_amdgcn_exp2f(t2);
+              const float u = fmaf(z, E, 1.f);
+              // what the rounding of 1 + z E dropped, as far as it matters: the logarithm needs
+              // du / u, which is du for u near 1 and, bounded so, below its rounding elsewhere
+              const float du = __builtin_amdgcn_fmed3f(fmaf(z, E, 1.f - u), -1.2e-7f, 1.2e-7f);
+              l = fmaf(du, 1.4426950408889634f, __builtin_amdgcn_logf(fmaxf(u, 1e-6f * E)));
+            } else {
+              l = __builtin_amdgcn_logf(fmaxf(z + __builtin_amdgcn_exp2f(-t2), 1e-6f));
+            }
+            acc[k] = fmaf(c_mw, l, acc[k]);
+          }
         }
-      }
+      };
+      if (thick)
+        update(std::false_type{});
+      else
+        update(std::true_type{});
     } else {
       gptr<float> o = G(p.out) + (size_t)s * nx * ny;
 #pragma unroll
@@ -200,7 +231,7 @@ __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
       if (live[k % kPerRow] && x < nx && y < ny) {
         float id = inv_den;
         if constexpr (XDEP) id = ldg(G(p.xden), (unsigned)x);
-        const float t = -acc[k] * id;
+        const float t = fmaf(-acc[k], id, thick ? 0.f : tv[k]);
         bad = bad || !(fabsf(t) <= 3.40282347e38f);
         stg(G(p.tau), (unsigned)(__mul24(y, nx) + x), t);
         if (p.phase_out) stg(G(p.phase_out), (unsigned)(__mul24(y, nx) + x), pc * t);
