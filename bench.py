@@ -54,19 +54,19 @@ def stage_bytes(stage, ny, nx, L, f=1):
     """Algorithmic HBM bytes of one problem's share of a stage launch (float32 / complex64):
     every array the stage must read or write, once; halo re-reads are not counted.  ny x nx is
     the detector; with oversampling f the stages work on the (f ny) x (f nx) internal grid, the
-    splat / closure write every line's prediction and the bin-split stage forms the residual."""
+    splat / closure bin every line's prediction and form the residual at the detector."""
     P = ny * nx * f * f
     H = f * ny * (f * nx // 2 + 1)  # half-spectrum bins per line
-    pred = 4 * P + 4 * L * P if f > 1 else 8 * P + 4 * L * P
+    pred = 4 * P + 4 * ny * nx + 4 * L * P
     return {
         "maxgrad": 4 * P,                       # read tau
-        "splat": pred,                          # read tau (and d); write e_s or P_s
+        "splat": pred,                          # read tau and d; write e_s
         "local": pred,
         "rowfft": 4 * P + 4 * L * P + 8 * L * H,  # read tau, e_s; write spectra
         "colfft": 16 * L * H,                   # read + write spectra
         "rowinv": 8 * L * H + 8 * P,            # read spectra, tau; write tau
         "vjp": 0,
-        "binsplit": 8 * L * P + 4 * ny * nx,    # read P_s, write e_s, read d
+        "binsplit": 0,                          # (part of the splat and the closure)
     }[stage]
 
 
@@ -442,7 +442,7 @@ def main():
     stage_share = {s: round(v / max(sum(stage_ms.values()), 1e-12), 4)
                    for s, v in stage_ms.items() if v > 0}
     stages = (("maxgrad", "splat") if model == "nonlocal" else ("local",))
-    stages += (("binsplit",) if f > 1 else ()) + ("rowfft", "colfft", "rowinv")
+    stages += ("rowfft", "colfft", "rowinv")
     alg_iter = sum(stage_bytes(s, p[2].ny, p[2].nx, L, f) for p in probs for s in stages)
     whole = alg_iter * n_iter / dt / 1e9
     per_sorted = sorted(per_step)

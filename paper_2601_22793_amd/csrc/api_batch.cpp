@@ -14,12 +14,11 @@ std::vector<int> batch_stages(int model, int f) {
   const bool transport = model == EPR_NONLOCAL || model == EPR_NONLOCAL_L2;
   if (transport) {
     v.push_back(kBsMaxg);
-    v.push_back(model == EPR_NONLOCAL && f == 1 ? kBsSplatSplit : kBsSplatLines);
-    if (model == EPR_NONLOCAL_L2) v.push_back(f == 1 ? kBsWkb1Split : kBsWkb1Lines);
+    if (model == EPR_NONLOCAL) v.push_back(f == 1 ? kBsSplatSplit : kBsSplatBin);
+    else v.insert(v.end(), {kBsSplatLines, f == 1 ? kBsWkb1Split : kBsWkb1Bin});
   } else {
-    v.push_back(f == 1 ? kBsLocalSplit : kBsLocalLines);
+    v.push_back(f == 1 ? kBsLocalSplit : kBsLocalBin);
   }
-  if (f > 1) v.push_back(kBsBinSplit);
   v.push_back(transport ? kBsRowGather : kBsRowCopy);
   v.push_back(kBsColFft);
   v.push_back(kBsRowInv);
@@ -30,12 +29,12 @@ int stage_blocks(int stage, const ProbDesc& p) {
   switch (stage) {
     case kBsMaxg: return blocks_maxg(p);
     case kBsSplatSplit:
-    case kBsSplatLines: return blocks_splat(p);
+    case kBsSplatLines:
+    case kBsSplatBin: return blocks_splat(p);
     case kBsLocalSplit:
-    case kBsLocalLines:
+    case kBsLocalBin:
     case kBsWkb1Split:
-    case kBsWkb1Lines: return blocks_local(p);
-    case kBsBinSplit: return blocks_binsplit(p);
+    case kBsWkb1Bin: return blocks_local(p);
     case kBsRowGather:
     case kBsRowCopy: return blocks_rowfft(p);
     case kBsColFft: return blocks_colfft(p);
@@ -88,27 +87,24 @@ int enqueue_batched(epr_ctx* h, hipStream_t cs, std::vector<epr_ctx::EvPair>* si
             break;
           case kBsSplatSplit:
           case kBsSplatLines:
-            a.mode = bp.stages[st_i] == kBsSplatSplit ? kSplatSplit : kSplatLines;
+          case kBsSplatBin:
+            a.mode = bp.stages[st_i] == kBsSplatSplit ? kSplatSplit
+                     : bp.stages[st_i] == kBsSplatBin ? kSplatBin : kSplatLines;
             rc = run_stage(h, kStSplat, gs, sk,
                            [&] { return launch_splat(a, grid, G.lds_sp, gs, bp.L); }, cls);
             break;
           case kBsLocalSplit:
-          case kBsLocalLines:
+          case kBsLocalBin:
           case kBsWkb1Split:
-          case kBsWkb1Lines: {
+          case kBsWkb1Bin: {
             const int k = bp.stages[st_i];
-            a.mode = (k == kBsLocalSplit || k == kBsWkb1Split) ? kLocalSplit : kLocalLines;
-            const int order = (k == kBsWkb1Split || k == kBsWkb1Lines) ? kOrderTransportWkb1
-                                                                        : bp.order;
+            a.mode = (k == kBsLocalSplit || k == kBsWkb1Split) ? kLocalSplit : kLocalBin;
+            const int order = (k == kBsWkb1Split || k == kBsWkb1Bin) ? kOrderTransportWkb1 : bp.order;
             rc = run_stage(h, kStLocal, gs, sk, [&] {
               return launch_local(a, grid, gs, order, bp.L, G.lrows);
             }, cls);
             break;
           }
-          case kBsBinSplit:
-            rc = run_stage(h, kStBinSplit, gs, sk,
-                           [&] { return launch_binsplit(a, grid, gs, bp.L, bp.os); }, cls);
-            break;
           case kBsRowGather:
           case kBsRowCopy:
             a.mode = bp.stages[st_i] == kBsRowGather ? kRowGatherFft : kRowCopyFft;
@@ -126,7 +122,8 @@ int enqueue_batched(epr_ctx* h, hipStream_t cs, std::vector<epr_ctx::EvPair>* si
         }
         const int k = bp.stages[st_i];
         if (rc == EPR_OK && bp.want_resid && g == bp.resid_group && it < 256 &&
-            (k == kBsSplatSplit || k == kBsLocalSplit || k == kBsWkb1Split || k == kBsBinSplit)) {
+            (k == kBsSplatSplit || k == kBsSplatBin || k == kBsLocalSplit || k == kBsLocalBin ||
+             k == kBsWkb1Split || k == kBsWkb1Bin)) {
           // the stage that formed the residual: reduce problem 0's partials into its slot
           const hipError_t e = launch_resid_reduce(single(bp.resid_desc, 0),
                                                    static_cast<float*>(h->hist.ptr) + it,
@@ -258,7 +255,7 @@ int solve_batched_impl(epr_ctx* h, int32_t n, const epr_problem* problems,
         descs[i].xcol = reinterpret_cast<const float4*>(xb);
         descs[i].xden = reinterpret_cast<const float*>(xb + cb);
       }
-      descs[i].os = f;
+      set_oversample(&descs[i], f);
       descs[i].X = q.thickness;
       descs[i].Y = q.thickness;
       descs[i].d = q.intensity;

@@ -314,12 +314,12 @@ int epr_forward_oversampled(epr_handle h, const epr_geometry* geom, const epr_sp
   CHECK(fill_desc(h, gi, lp, static_cast<char*>(h->ws.ptr), &p));
   p.X = absorb;
   p.Y = phase;
-  p.os = oversample;
+  set_oversample(&p, oversample);
   p.d = nullptr;         // the bin-split pass writes the binned prediction to out
   p.out = intensity;
   p.resid = nullptr;
   const int cls = spectral_threads(p) == 1024 ? 1 : 0;
-  CHECK(launch_lines_binsplit(h, p, model, st, nullptr, cls));
+  CHECK(launch_predict_bin(h, p, model, st, nullptr, cls));
   h->last_stream = st;
   return EPR_OK;
 }

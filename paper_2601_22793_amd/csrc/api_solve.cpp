@@ -40,7 +40,7 @@ int epr_solve(epr_handle h, const epr_geometry* geom, const epr_spectrum* spec,
   p.d = intensity;
   p.tau = thickness;
   p.relax = (float)opts->relaxation;
-  p.os = f;
+  set_oversample(&p, f);
   const bool want_resid = (opts->flags & EPR_FLAG_RESIDUALS) != 0;
   if (!want_resid) p.resid = nullptr;
   p.status = static_cast<unsigned*>(h->status.ptr);
@@ -109,7 +109,7 @@ int epr_solve_noalloc(epr_handle h, const epr_geometry* geom, const epr_spectrum
   p.d = intensity;
   p.tau = thickness;
   p.relax = (float)opts->relaxation;
-  p.os = f;
+  set_oversample(&p, f);
   const bool want_resid = (opts->flags & EPR_FLAG_RESIDUALS) != 0;
   if (!want_resid) p.resid = nullptr;
   p.status = static_cast<unsigned*>(h->status.ptr);
@@ -194,7 +194,7 @@ int epr_solve_xspec(epr_handle h, const epr_geometry* geom, const epr_spectrum* 
   p.d = intensity;
   p.tau = thickness;
   p.relax = (float)opts->relaxation;
-  p.os = f;
+  set_oversample(&p, f);
   p.xcol = xcol;
   p.xden = den;
   apply_row_lines(h, &p);

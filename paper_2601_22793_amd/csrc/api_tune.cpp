@@ -184,7 +184,7 @@ int epr_autotune(epr_handle h, int32_t n, const epr_problem* problems, const epr
     p->X = p->Y = p->tau = tau;
     p->d = q.intensity;
     p->relax = (float)opts->relaxation;
-    p->os = f;
+    set_oversample(p, f);
     p->resid = nullptr;
     p->status = nullptr;
     apply_row_lines(h, p);

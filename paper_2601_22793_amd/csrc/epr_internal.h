@@ -152,10 +152,10 @@ struct KArgs {
 };
 
 // Modes
-enum SplatMode { kSplatForward = 0, kSplatSplit = 1, kSplatLines = 2 };
+enum SplatMode { kSplatForward = 0, kSplatSplit = 1, kSplatLines = 2, kSplatBin = 3 };
 enum RowMode { kRowGatherFft = 0, kRowCopyFft = 1, kRowGatherOnly = 2 };
 enum RowInvMode { kRowInvSolve = 0, kRowInvPrecond = 1 };
-enum LocalMode { kLocalForward = 0, kLocalSplit = 1, kLocalLines = 2 };
+enum LocalMode { kLocalForward = 0, kLocalSplit = 1, kLocalBin = 2 };
 // closure order of the local kernel: 1, 2 (Eq. 1), or the diffraction-pressure term added to
 // the transported per-line predictions held in e (second-order non-local model)
 constexpr int kOrderTransportWkb1 = 3;
@@ -194,10 +194,6 @@ inline int local_rows(int blocks16, int lines) {
   const int waves = blocks16 * lines * local_strips(lines);
   return waves < 256 ? 4 : (waves < 1024 || lines >= 16) ? 8 : 16;
 }
-// detector-level residual on an oversampled grid: one detector pixel per thread, 256 threads
-__host__ __device__ inline int blocks_binsplit(const ProbDesc& p) {
-  return ((p.ny / p.os) * (p.nx / p.os) + 255) / 256;
-}
 
 // LDS bytes of each kernel for a problem
 inline size_t lds_splat(const ProbDesc& p) {
@@ -232,7 +228,6 @@ hipError_t launch_rowfft(const KArgs& a, int total_blocks, size_t lds, hipStream
 hipError_t launch_colfft(const KArgs& a, int total_blocks, size_t lds, hipStream_t s, int nt);
 hipError_t launch_rowinv(const KArgs& a, int total_blocks, size_t lds, hipStream_t s, int nt);
 hipError_t launch_resid_reduce(const KArgs& a, float* hist_slot, int nb, hipStream_t s);
-hipError_t launch_binsplit(const KArgs& a, int total_blocks, hipStream_t s, int lines, int f);
 // r [lines][ny/f][nx/f] -> out [lines][ny][nx]: each value over its f x f pixels, times 1/f^2
 hipError_t launch_unbin_lines(const float* r, float* out, int ny, int nx, int f, int lines,
                               hipStream_t s);

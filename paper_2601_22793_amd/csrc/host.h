@@ -199,12 +199,11 @@ struct DeviceGuard {
   } while (0)
 
 enum Stage { kStMaxg = 0, kStSplat = 1, kStLocal = 2, kStRowFft = 3, kStColFft = 4,
-             kStRowInv = 5, kStVjp = 6, kStBinSplit = 7 };
+             kStRowInv = 5, kStVjp = 6 };  // (stage 7, the bin-split pass, is part of 1 and 2)
 
 // Launches of a batched iteration.
-enum BatchStage { kBsMaxg, kBsSplatSplit, kBsSplatLines, kBsLocalSplit, kBsLocalLines,
-                  kBsWkb1Split, kBsWkb1Lines, kBsBinSplit, kBsRowGather, kBsRowCopy, kBsColFft,
-                  kBsRowInv };
+enum BatchStage { kBsMaxg, kBsSplatSplit, kBsSplatLines, kBsSplatBin, kBsLocalSplit, kBsLocalBin,
+                  kBsWkb1Split, kBsWkb1Bin, kBsRowGather, kBsRowCopy, kBsColFft, kBsRowInv };
 
 enum class Kind { Solve, Maps };
 
@@ -257,10 +256,11 @@ int upload_xtable(epr_ctx* h, const XTable& t, hipStream_t st, const float4** co
                   const float** den, const float2** blk);
 int fill_desc(epr_ctx* h, const epr_geometry& g, const LineParams& lp, char* base, ProbDesc* p,
               const float2* row_tab = nullptr, const float2* col_tab = nullptr);
+void set_oversample(ProbDesc* p, int f);
 void apply_row_lines(const epr_ctx* h, ProbDesc* p);
 KArgs single(const ProbDesc& p, int mode);
 int launch_transport_lines(epr_ctx* h, const ProbDesc& p, hipStream_t st, int cls);
-int launch_lines_binsplit(epr_ctx* h, const ProbDesc& p, int model, hipStream_t st,
+int launch_predict_bin(epr_ctx* h, const ProbDesc& p, int model, hipStream_t st,
                           float* hist_slot, int cls);
 int launch_iteration(epr_ctx* h, const ProbDesc& p, int model, hipStream_t st, float* hist_slot);
 int check_ptr(epr_ctx* h, const void* p, const char* name);

@@ -525,6 +525,16 @@ int fill_desc(epr_ctx* h, const epr_geometry& g, const LineParams& lp, char* bas
   return EPR_OK;
 }
 
+// Internal grid of oversampling factor f.  The bin mode needs splat tiles of whole detector
+// pixels: a tuned tile that is not takes the default one's place.
+void set_oversample(ProbDesc* p, int f) {
+  p->os = f;
+  if (p->splat_tx % f || p->splat_ty % f) {
+    p->splat_tx = kSplatTileX;
+    p->splat_ty = kSplatTileY;
+  }
+}
+
 // The solves' row pass takes the tuned lines per workgroup.
 void apply_row_lines(const epr_ctx* h, ProbDesc* p) { p->rlpb = h->row_lines; }
 
@@ -548,33 +558,32 @@ int launch_transport_lines(epr_ctx* h, const ProbDesc& p, hipStream_t st, int cl
   }, cls);
 }
 
-// Predictions on an oversampled internal grid: every line's P_s into e, then the detector-level
-// sum, residual and split, replicated back onto the internal grid.
-int launch_lines_binsplit(epr_ctx* h, const ProbDesc& p, int model, hipStream_t st,
-                          float* hist_slot, int cls) {
+// Predictions on an oversampled internal grid with the detector-level sum, residual and split,
+// replicated back onto the internal grid (the last stage's bin mode).
+int launch_predict_bin(epr_ctx* h, const ProbDesc& p, int model, hipStream_t st, float* hist_slot,
+                       int cls) {
   auto* sink = &h->pending;
   int rc;
   if (model == EPR_NONLOCAL) {
-    rc = launch_transport_lines(h, p, st, cls);
-  } else if (model == EPR_NONLOCAL_L2) {
-    rc = launch_transport_lines(h, p, st, cls);
+    rc = run_stage(h, kStMaxg, st, sink,
+                   [&] { return launch_maxgrad(single(p, 0), blocks_maxg(p), st); }, cls);
     if (rc) return rc;
-    rc = run_stage(h, kStLocal, st, sink, [&] {
-      return launch_local(single(p, kLocalLines), blocks_local(p), st,
-                          kOrderTransportWkb1, p.lp.n, p.lrows);
+    rc = run_stage(h, kStSplat, st, sink, [&] {
+      return launch_splat(single(p, kSplatBin), blocks_splat(p), lds_splat(p), st, p.lp.n);
     }, cls);
   } else {
+    if (model == EPR_NONLOCAL_L2) {
+      rc = launch_transport_lines(h, p, st, cls);
+      if (rc) return rc;
+    }
+    const int order = model == EPR_NONLOCAL_L2 ? kOrderTransportWkb1 : model == EPR_LOCAL_L1 ? 1 : 2;
     rc = run_stage(h, kStLocal, st, sink, [&] {
-      return launch_local(single(p, kLocalLines), blocks_local(p), st,
-                          model == EPR_LOCAL_L1 ? 1 : 2, p.lp.n, p.lrows);
+      return launch_local(single(p, kLocalBin), blocks_local(p), st, order, p.lp.n, p.lrows);
     }, cls);
   }
   if (rc) return rc;
-  rc = run_stage(h, kStBinSplit, st, sink, [&] {
-    return launch_binsplit(single(p, 0), blocks_binsplit(p), st, p.lp.n, p.os);
-  }, cls);
-  if (rc) return rc;
-  if (hist_slot) HIP_TRY(h, launch_resid_reduce(single(p, 0), hist_slot, blocks_binsplit(p), st));
+  const int nb = model == EPR_NONLOCAL ? blocks_splat(p) : blocks_local(p);
+  if (hist_slot) HIP_TRY(h, launch_resid_reduce(single(p, 0), hist_slot, nb, st));
   return EPR_OK;
 }
 
@@ -584,7 +593,7 @@ int launch_iteration(epr_ctx* h, const ProbDesc& p, int model, hipStream_t st, f
   auto* sink = &h->pending;
   int rc;
   if (p.os > 1) {
-    rc = launch_lines_binsplit(h, p, model, st, hist_slot, cls);
+    rc = launch_predict_bin(h, p, model, st, hist_slot, cls);
     if (rc) return rc;
     rc = run_stage(h, kStRowFft, st, sink, [&] {
       return launch_rowfft(single(p, transport_model(model) ? kRowGatherFft : kRowCopyFft),

@@ -23,8 +23,11 @@
 // 1080 x 1200, 4 lines: 159 -> 29 us a launch; 256 x 256, 1 line: 8.4 -> 6.9 us.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "dev_common.h"
 #include "epr_internal.h"
+#include "split_bin.h"
 
 namespace epr {
 
@@ -212,8 +215,6 @@ __device__ __forceinline__ void local_body(const ProbDesc& p, int local, int mod
     }
     if (mode == kLocalForward) {
       stg(G(p.out), pix, P);
-    } else if (mode == kLocalLines) {
-      for (int s = 0; s < L; ++s) stg(G(p.e) + (size_t)s * nx * ny, pix, Pr[s * ls]);
     } else {
       const float dv = R <= 8 ? dq : ldg(G((const float*)p.d), pix);
       const float e = dv - P;
@@ -229,14 +230,34 @@ __device__ __forceinline__ void local_body(const ProbDesc& p, int local, int mod
       }
     }
   };
-  if constexpr (R <= 8) {
+  if (mode == kLocalBin) {
+    // an oversampled internal grid: the residual and split at the detector pixels (strips are
+    // whole detector pixels), one detector row of a strip per wave and step
+    auto bin = [&](auto factor) {
+      constexpr int F = decltype(factor)::value;
+      static_assert(kLocalCols % F == 0 && R % F == 0, "whole detector pixels");
+      for (int q = w; q < R / F * ns; q += nw) {
+        const int r0 = q / ns * F, j = q - q / ns * ns;
+        const int y = y0 + r0, x = tx0 + j * kLocalCols + lane * F;
+        if (lane >= kLocalCols / F || y >= ny || x >= nx) continue;
+        const float* Pr = Pl + (j * R + r0) * 64 + kLH + lane * F;
+        split_bin<kMaxLines, F, XDEP>(p, y, x, [&](int r, int c, int s) {
+          return Pr[s * ns * R * 64 + r * 64 + c];
+        }, se, sd);
+      }
+    };
+    if (p.os == 2)
+      bin(std::integral_constant<int, 2>{});
+    else
+      bin(std::integral_constant<int, 4>{});
+  } else if constexpr (R <= 8) {
 #pragma unroll
     for (int k = 0; k < R; ++k)
       if (w + k * nw < R * ns) sum_row(w + k * nw, dpre[k]);
   } else {
     for (int q = w; q < R * ns; q += nw) sum_row(q, 0.f);
   }
-  if (mode == kLocalSplit && p.resid != nullptr) {
+  if ((mode == kLocalSplit || mode == kLocalBin) && p.resid != nullptr) {
     __shared__ float red[2][kMaxLines];
     se = wave_sum(se);
     sd = wave_sum(sd);

@@ -7,6 +7,7 @@
 
 #include "dev_common.h"
 #include "epr_internal.h"
+#include "split_bin.h"
 
 namespace epr {
 
@@ -147,6 +148,8 @@ __global__ __launch_bounds__(kMaxgThreads) void k_maxgrad(KArgs a, const ProbDes
 //   forward mode: out = sum_s P_s
 //   split mode  : e = d - sum_s P_s, e_s = pi_s e with pi_s = max(P_s,0)/sum max(P_s',0)
 //                 (w_s where that sum is zero), written to e[s]; optional residual partials.
+//   bin mode    : the same on an oversampled internal grid (split_bin): P_s is the mean over the
+//                 f x f internal pixels of a detector pixel, e_s goes to all of them.
 // NL bounds the line count at compile time so that the per-line constants sit in registers
 // for the whole source loop: a scalar load inside the loop would make every iteration wait
 // for all outstanding LDS atomics (they share one counter).
@@ -491,7 +494,28 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
         }
       }
     };
-    if constexpr (FULL) {
+    if (mode == kSplatBin) {
+      // (tiles are whole detector pixels: bin_tile)
+      auto line_at = [&](int o, int s) {
+        return (FULL || fixed) ? (float)acc_u[s * ptk + o] * inv_scale[s] : acc_f[s * ptk + o];
+      };
+      auto bin = [&](auto factor) {
+        constexpr int F = decltype(factor)::value;
+        const int tw = TXk / F;
+        for (int i = tid; i < tw * (TYk / F); i += kSplatThreads) {
+          const int ly = i / tw * F, lx = (i - i / tw * tw) * F;
+          const int y = ty0 + ly, x = tx0 + lx;
+          if (y < ny && x < nx)
+            split_bin<NL, F, XDEP>(p, y, x, [&](int r, int c, int s) {
+              return line_at((ly + 1 + r) * PXk + lx + 1 + c, s);
+            }, se, sd);
+        }
+      };
+      if (p.os == 2)
+        bin(std::integral_constant<int, 2>{});
+      else
+        bin(std::integral_constant<int, 4>{});
+    } else if constexpr (FULL) {
 #pragma unroll
       for (int k = 0; k < kPre; ++k) read_back(tid + k * kSplatThreads, dpre[k]);
     } else {
@@ -507,7 +531,7 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
   } else {
     tile(std::false_type{}, std::false_type{});
   }
-  if (mode == kSplatSplit && p.resid != nullptr) {
+  if (mode != kSplatForward && mode != kSplatLines && p.resid != nullptr) {
     __syncthreads();
     se = wave_sum(se);
     sd = wave_sum(sd);
@@ -526,112 +550,6 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
       G(p.resid)[2 * local + 1] = td;
     }
   }
-}
-
-// ---------------------------------------------------------------------------------------------
-// Detector-level sum, residual and split on an oversampled internal grid.  e holds each line's
-// prediction P_s on the internal grid (ny x nx); every thread owns one detector pixel: it bins
-// the f x f internal pixels of each line (their mean), sums the lines, forms e = d - P and the
-// positivity-weighted split e_s, and writes e_s to the same f x f internal pixels (replication),
-// in place.  Residual partial sums as in the splat.
-// ---------------------------------------------------------------------------------------------
-template <int NL, int F>
-__device__ __forceinline__ void binsplit_body(const ProbDesc& p, int local, int) {
-  const int nx = p.nx, ny = p.ny;
-  const int nxd = nx / F, nyd = ny / F;
-  const int L = p.lp.n;
-  const int i = local * 256 + threadIdx.x;
-  float se = 0.f, sd = 0.f;
-  if (i < nyd * nxd) {
-    const int Y = i / nxd, X = i - Y * nxd;
-    const unsigned base = (unsigned)(__mul24(F * Y, nx) + F * X);
-    gptr<float> e = G(p.e);
-    float Pv[NL];
-    float P = 0.f, S = 0.f;
-#pragma unroll
-    for (int s = 0; s < NL; ++s) {
-      Pv[s] = 0.f;
-      if (s < L) {
-        gptr<const float> es = (gptr<const float>)(e + (size_t)s * nx * ny);
-        float acc = 0.f;
-#pragma unroll
-        for (int r = 0; r < F; ++r)
-#pragma unroll
-          for (int c = 0; c < F; ++c) acc += ldg(es, base + (unsigned)(r * nx + c));
-        Pv[s] = acc * (1.f / (F * F));
-      }
-      P += Pv[s];
-      S += fmaxf(Pv[s], 0.f);
-    }
-    if (p.d == nullptr) {
-      // forward model only: the detector intensity, no residual
-      stg(G(p.out), (unsigned)i, P);
-    } else {
-      const float dv = ldg(G((const float*)p.d), (unsigned)i);
-      const float ev = dv - P;
-      se = ev * ev;
-      sd = dv * dv;
-      const bool hole = !(S > 1e-30f);
-      const float inv = hole ? 0.f : 1.f / S;
-#pragma unroll
-      for (int s = 0; s < NL; ++s) {
-        if (s < L) {
-          float fw = p.lp.w[s];
-          if (hole && p.xcol) {
-            // x-dependent spectrum: the line's weight averaged over the f internal columns
-            fw = 0.f;
-#pragma unroll
-            for (int c = 0; c < F; ++c) fw += xcol_at(p, F * X + c, s).x;
-            fw *= 1.f / F;
-          }
-          const float v = (hole ? fw : fmaxf(Pv[s], 0.f) * inv) * ev;
-          gptr<float> es = e + (size_t)s * nx * ny;
-#pragma unroll
-          for (int r = 0; r < F; ++r)
-#pragma unroll
-            for (int c = 0; c < F; ++c) stg(es, base + (unsigned)(r * nx + c), v);
-        }
-      }
-    }
-  }
-  if (p.resid != nullptr && p.d != nullptr) {
-    __shared__ float red[2][4];
-    se = wave_sum(se);
-    sd = wave_sum(sd);
-    if ((threadIdx.x & 63) == 0) {
-      red[0][threadIdx.x >> 6] = se;
-      red[1][threadIdx.x >> 6] = sd;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      G(p.resid)[2 * local] = red[0][0] + red[0][1] + red[0][2] + red[0][3];
-      G(p.resid)[2 * local + 1] = red[1][0] + red[1][1] + red[1][2] + red[1][3];
-    }
-  }
-}
-
-template <bool B, int NL, int F>
-__global__ __launch_bounds__(256) void k_binsplit(KArgs a, const ProbDesc* __restrict__ table) {
-  EPR_DISPATCH(B, a, table, blockIdx.x, (binsplit_body<NL, F>), 0);
-}
-
-template <int NL, int F>
-void launch_binsplit_nf(const KArgs& a, int total_blocks, hipStream_t s) {
-  if (a.table)
-    hipLaunchKernelGGL((k_binsplit<true, NL, F>), dim3(total_blocks), dim3(256), 0, s, a, a.table);
-  else
-    hipLaunchKernelGGL((k_binsplit<false, NL, F>), dim3(total_blocks), dim3(256), 0, s, a, a.table);
-}
-
-template <int NL>
-hipError_t launch_binsplit_n(const KArgs& a, int total_blocks, hipStream_t s, int f) {
-  if (f == 2)
-    launch_binsplit_nf<NL, 2>(a, total_blocks, s);
-  else if (f == 4)
-    launch_binsplit_nf<NL, 4>(a, total_blocks, s);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
 }
 
 // Transpose of the detector binning for every line: the detector values r[s] copied to their
@@ -655,16 +573,6 @@ hipError_t launch_unbin_lines(const float* r, float* out, int ny, int nx, int f,
   hipLaunchKernelGGL(k_unbin_lines, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, r, out,
                      ny, nx, f, lines);
   return hipGetLastError();
-}
-
-// f: the oversampling factor of the launch's problems (2 or 4).  A problem with no data
-// (p.d null) gets its binned prediction in p.out instead of a split residual.
-hipError_t launch_binsplit(const KArgs& a, int total_blocks, hipStream_t s, int lines, int f) {
-  if (lines <= 1) return launch_binsplit_n<1>(a, total_blocks, s, f);
-  if (lines <= 2) return launch_binsplit_n<2>(a, total_blocks, s, f);
-  if (lines <= 4) return launch_binsplit_n<4>(a, total_blocks, s, f);
-  if (lines <= 8) return launch_binsplit_n<8>(a, total_blocks, s, f);
-  return launch_binsplit_n<16>(a, total_blocks, s, f);
 }
 
 template <bool B, int NL>
