@@ -33,35 +33,26 @@ int xspec_maps_setup(epr_ctx* h, const epr_geometry* geom, const epr_spectrum* s
   return EPR_OK;
 }
 
-// Workspace bytes of the vector-Jacobian product: G_x, G_y, and for the second-order models
-// two sets of per-line planes.
-size_t vjp_workspace(const epr_ctx* h, int ny, int nx, int n_lines) {
-  const WsLayout w = ws_layout(ny, nx, n_lines, h->splat_tx, h->splat_ty);
-  const size_t plane = (size_t)ny * nx;
-  return std::max(w.total, align256(sizeof(float) * (2 + 2 * (size_t)n_lines) * plane));
-}
+// Workspace bytes of the vector-Jacobian product: G_x and G_y of the local closures.
+size_t vjp_workspace(int ny, int nx) { return align256(sizeof(float) * 2 * (size_t)ny * nx); }
 
 // The VJP kernels of `model` for p (X, Y and d = dL/dP set): grad_a = sum_s -a_s I_s dI_s,
 // then grad_y = D_x^T G_x + D_y^T G_y, or with `accumulate` (grad_y == grad_a, an x-dependent
 // spectrum over one thickness map) that sum added to grad_a.  The workspace is h->ws.
 int vjp_stages(epr_ctx* h, const ProbDesc& p, int model, hipStream_t st, float* grad_y,
                float* grad_a, bool accumulate) {
-  const size_t plane = (size_t)p.ny * p.nx;
   float* gx = static_cast<float*>(h->ws.ptr);
-  float* gy = gx + plane;
-  float* work = gy + plane;
-  float* qpl = work + p.lp.n * plane;
-  const int nb = (int)((plane + 255) / 256);
+  float* gy = gx + (size_t)p.ny * p.nx;
+  const KArgs a = single(p, 0);
   return run_stage(h, kStVjp, st, &h->pending, [&] {
-    hipError_t e = hipSuccess;
-    if (model == EPR_NONLOCAL || model == EPR_NONLOCAL_L2)
-      e = launch_vjp(single(p, 0), nb, 0, st, gx, gy, grad_a);
-    if (e == hipSuccess && model != EPR_NONLOCAL) {
-      const int order = model == EPR_LOCAL_L1 ? 1 : model == EPR_LOCAL_L2 ? 2 : 3;
-      e = launch_vjp_local(single(p, 0), nb, st, order, work, qpl, gx, gy, grad_a);
+    if (transport_model(model)) {
+      const hipError_t e = launch_vjp(a, st, grad_y, grad_a, accumulate ? 1 : 0);
+      if (e != hipSuccess || model == EPR_NONLOCAL) return e;
+      return launch_vjp_local(a, st, kOrderTransportWkb1, nullptr, nullptr, grad_a);
     }
+    const hipError_t e = launch_vjp_local(a, st, model == EPR_LOCAL_L1 ? 1 : 2, gx, gy, grad_a);
     if (e != hipSuccess) return e;
-    return launch_vjp_transpose(single(p, 0), nb, st, gx, gy, grad_y, accumulate ? 1 : 0);
+    return launch_vjp_transpose(a, st, gx, gy, grad_y, accumulate ? 1 : 0);
   });
 }
 
@@ -387,7 +378,7 @@ int epr_forward_vjp(epr_handle h, const epr_geometry* geom, const epr_spectrum* 
   DeviceGuard guard(h->device);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const LineParams lp = line_params(*geom, *spec, nullptr, Kind::Maps);
-  CHECK(ensure(h, h->ws, vjp_workspace(h, geom->ny, geom->nx, lp.n)));
+  CHECK(ensure(h, h->ws, vjp_workspace(geom->ny, geom->nx)));
   ProbDesc p;
   CHECK(fill_desc(h, *geom, lp, nullptr, &p));
   p.X = absorb;
@@ -428,7 +419,7 @@ int epr_forward_vjp_oversampled(epr_handle h, const epr_geometry* geom, const ep
   const epr_geometry gi = internal_geometry(*geom, oversample);
   const LineParams lp = line_params(gi, *spec, nullptr, Kind::Maps);
   // the VJP's planes, then the detector gradient spread over the internal grid
-  const size_t base = align256(vjp_workspace(h, gi.ny, gi.nx, lp.n));
+  const size_t base = vjp_workspace(gi.ny, gi.nx);
   const size_t plane = (size_t)gi.ny * gi.nx;
   CHECK(ensure(h, h->ws, base + sizeof(float) * plane));
   float* g_int = reinterpret_cast<float*>(static_cast<char*>(h->ws.ptr) + base);
@@ -456,7 +447,7 @@ int epr_forward_xspec_vjp(epr_handle h, const epr_geometry* geom, const epr_spec
   hipStream_t st = static_cast<hipStream_t>(stream);
   ProbDesc p;
   CHECK(xspec_maps_setup(h, geom, spec, profile, mat, model, thickness, st, nullptr, &p));
-  CHECK(ensure(h, h->ws, vjp_workspace(h, geom->ny, geom->nx, p.lp.n)));
+  CHECK(ensure(h, h->ws, vjp_workspace(geom->ny, geom->nx)));
   p.d = grad_intensity;
   CHECK(vjp_stages(h, p, model, st, grad_thickness, grad_thickness, true));
   h->last_stream = st;

@@ -145,6 +145,15 @@ __device__ __forceinline__ float lane64_max(float v) {
 }
 #undef EPR_DPP_MAX
 
+// value of the lane to the left (lane - 1) and to the right (lane + 1); the wave's first / last
+// lane reads zero (the kernels keep a halo lane there)
+__device__ __forceinline__ float lane_left(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_right(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
+}
+
 // Halo (in pixels, per axis) that covers every source whose bilinear footprint can reach a
 // tile: H = floor(max |u|) + 1, with max |u| = max_s |b_s| * max |D Y| (rounding is monotone,
 // so this bounds every per-source shift computed as b_s * D Y).  Capped at the image size.

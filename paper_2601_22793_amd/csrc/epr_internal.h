@@ -231,17 +231,17 @@ hipError_t launch_resid_reduce(const KArgs& a, float* hist_slot, int nb, hipStre
 // r [lines][ny/f][nx/f] -> out [lines][ny][nx]: each value over its f x f pixels, times 1/f^2
 hipError_t launch_unbin_lines(const float* r, float* out, int ny, int nx, int f, int lines,
                               hipStream_t s);
-hipError_t launch_vjp(const KArgs& a, int total_blocks, size_t lds, hipStream_t s, float* gx,
-                      float* gy, float* ga);
-// local closures (order 1, 2) or the pressure term added to the non-local gradients (order 3);
-// work and q: [L][ny][nx] scratch planes (order >= 2).  Both VJP launchers read the line
-// constants per column when a.p.xcol is set (x-dependent spectrum, X = Y = thickness).
-hipError_t launch_vjp_local(const KArgs& a, int total_blocks, hipStream_t s, int order,
-                            float* work, float* q, float* gx, float* gy, float* ga);
+// Non-local model: gphase = D_x^T G_x + D_y^T G_y and ga, or (accumulate != 0) their sum into
+// gphase.
+hipError_t launch_vjp(const KArgs& a, hipStream_t s, float* gphase, float* ga, int accumulate);
+// Local closures (order 1, 2: gx, gy, ga) or the pressure term added to the non-local gradient
+// ga (order 3).  Both VJP launchers read the line constants per column when a.p.xcol is set
+// (x-dependent spectrum, X = Y = thickness).
+hipError_t launch_vjp_local(const KArgs& a, hipStream_t s, int order, float* gx, float* gy,
+                            float* ga);
 // gphase = D_x^T gx + D_y^T gy, or (accumulate != 0) gphase += that
-hipError_t launch_vjp_transpose(const KArgs& a, int total_blocks, hipStream_t s,
-                                const float* gx, const float* gy, float* gphase,
-                                int accumulate);
+hipError_t launch_vjp_transpose(const KArgs& a, hipStream_t s, const float* gx, const float* gy,
+                                float* gphase, int accumulate);
 // Fixed scratch of the allocation-free solve (noalloc.hip): the device address of this GPU's
 // copy of the scratch array (`device` must be the current device on the first call for it),
 // and a W_n^j table (j < n) written into it by a kernel.
@@ -251,6 +251,5 @@ hipError_t set_transport_attributes();
 hipError_t set_rowfft_attributes();
 hipError_t set_colfft_attributes();
 hipError_t set_rowinv_attributes();
-hipError_t set_vjp_attributes();
 
 }  // namespace epr

@@ -834,7 +834,6 @@ int epr_create(epr_handle* out, int device) {
   (void)set_rowfft_attributes();
   (void)set_colfft_attributes();
   (void)set_rowinv_attributes();
-  (void)set_vjp_attributes();
   (void)set_regime_attributes();
   (void)hipGetLastError();
   if (hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) != hipSuccess ||

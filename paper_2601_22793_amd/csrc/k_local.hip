@@ -33,15 +33,6 @@ namespace epr {
 
 constexpr int kLH = kLocalHalo;
 
-// value of the lane to the left (lane - 1) and to the right (lane + 1); the wave's first / last
-// lane reads zero (its column is halo, never an output)
-__device__ __forceinline__ float lane_left(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float lane_right(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
-}
-
 // P_s of line s on the strip whose first output pixel is (y0, xs), into Pl[R][64] (lane columns).
 // EDGE: some derivative of the strip is one-sided (or a row or column lies off the image: the
 // values there are clamped reads that no output uses).  Otherwise every difference is central

@@ -11,16 +11,14 @@
 // The ray map is recomputed from the phase; nothing is kept from the forward call.
 //
 // XDEP: x-dependent spectrum (Methods 4.3 remark).  Both maps are the thickness tau, and
-// w_s, a_s (= mu_s), b_s and q_s are read at each pixel's column; the caller adds the transposed
-// shift gradients to grad_A (k_vjp_transpose with `accumulate`) to obtain dL/dtau.
+// w_s, a_s (= mu_s), b_s and q_s are read at each pixel's column; dL/dtau is then
+// grad_A + D_x^T G_x + D_y^T G_y (`accumulate`).
 #include <hip/hip_runtime.h>
 
 #include "dev_common.h"
 #include "epr_internal.h"
 
 namespace epr {
-
-constexpr int kVjpThreads = 256;
 
 // {w_s, a_s, b_s, q_s} of line s at column x
 template <bool XDEP>
@@ -29,76 +27,150 @@ __device__ __forceinline__ float4 line_wabq(const ProbDesc& p, int x, int s) {
   else return make_float4(p.lp.w[s], p.lp.a[s], p.lp.b[s], p.lp.q[s]);
 }
 
-template <bool XDEP>
-__global__ __launch_bounds__(kVjpThreads) void k_vjp(KArgs a, float* __restrict__ Gx,
-                                                     float* __restrict__ Gy,
-                                                     float* __restrict__ gA) {
-  const ProbDesc& p = a.p;
-  const int nx = p.nx, ny = p.ny, L = p.lp.n;
-  const int i = blockIdx.x * kVjpThreads + threadIdx.x;
-  if (i >= nx * ny) return;
-  const int y = i / nx, x = i - y * nx;
-  gptr<const float> g = G(p.d);  // incoming gradient dL/dP
-  const float gxs = d_x(G(p.Y), y, x, nx);
-  const float gys = d_y(G(p.Y), y, x, ny, nx);
-  const float av = G(p.X)[i];
-  float sa = 0.f, sx = 0.f, sy = 0.f;
-  for (int s = 0; s < L; ++s) {
-    const float4 c = line_wabq<XDEP>(p, x, s);
-    const float I = c.x * expf(-c.y * av);
-    const float bs = c.z;
-    const float ux = bs * gxs, uy = bs * gys;
-    // cell and in-cell position as the splat forms them
-    const float dx = __builtin_amdgcn_fractf(ux), dy = __builtin_amdgcn_fractf(uy);
-    const int x0 = x + floor_to_int(ux), y0 = y + floor_to_int(uy);
-    float g00 = 0.f, g10 = 0.f, g01 = 0.f, g11 = 0.f;  // g_ij: paper's tap w_ij
-    const bool xin0 = x0 >= 0 && x0 < nx, xin1 = x0 + 1 >= 0 && x0 + 1 < nx;
-    if (y0 >= 0 && y0 < ny) {
-      if (xin0) g00 = g[(size_t)y0 * nx + x0];
-      if (xin1) g10 = g[(size_t)y0 * nx + x0 + 1];
-    }
-    if (y0 + 1 >= 0 && y0 + 1 < ny) {
-      if (xin0) g01 = g[(size_t)(y0 + 1) * nx + x0];
-      if (xin1) g11 = g[(size_t)(y0 + 1) * nx + x0 + 1];
-    }
-    const float gI = (1.f - dy) * ((1.f - dx) * g00 + dx * g10) + dy * ((1.f - dx) * g01 + dx * g11);
-    const float gux = I * ((1.f - dy) * (g10 - g00) + dy * (g11 - g01));
-    const float guy = I * ((1.f - dx) * (g01 - g00) + dx * (g11 - g10));
-    sa -= c.y * I * gI;
-    sx += bs * gux;
-    sy += bs * guy;
-  }
-  gA[i] = sa;
-  Gx[i] = sx;
-  Gy[i] = sy;
+// Transpose of D along one axis of length n at index j, from the values at j - 1, j and j + 1:
+// D has rows (-1, 1) at 0, (-1/2, 0, 1/2) inside and (-1, 1) at n - 1.
+__device__ __forceinline__ float d_transpose3(float l, float m, float r, int j, int n) {
+  if (j == 0) return -m - 0.5f * r;
+  if (j == n - 1) return 0.5f * l + m;
+  return (j == 1 ? l : 0.5f * l) - (j == n - 2 ? r : 0.5f * r);
 }
 
-// Transpose of D along one axis of length n applied to g at index j (row-major access through
-// `at`): D has rows (-1, 1) at 0, (-1/2, 0, 1/2) inside and (-1, 1) at n-1.
-template <class F>
-__device__ __forceinline__ float d_transpose(F at, int j, int n) {
-  if (j == 0) return -at(0) - 0.5f * at(1);
-  if (j == 1) return at(0) - 0.5f * at(2);
-  if (j == n - 2) return 0.5f * at(n - 3) - at(n - 1);
-  if (j == n - 1) return 0.5f * at(n - 2) + at(n - 1);
-  return 0.5f * (at(j - 1) - at(j + 1));
+// ---------------------------------------------------------------------------------------------
+// Non-local model.  A workgroup of 8 waves computes G and the absorption gradient on a region of
+// 64 x 32 pixels, a lane one column of 4 consecutive rows, and writes both gradients on the
+// 62 x 30 pixels inside: D_x^T G_x from the neighbouring lanes, D_y^T G_y through LDS, so G is never
+// in memory (the 10 % computed twice cost less than a pass that reads G back).  The lines are
+// the outer loop: 16 taps of g are in flight per lane, read at one offset per pixel from
+// wave-uniform bases when a wave vote finds all of them inside the image.
+// 2048 x 2048, 8 lines:
+// 76 + 16 us (with the transposes as a second pass) -> 67 us.  Bound by the L1: the taps take 36
+// cache accesses per 64 pixels and line, with 44 vector issue slots beside them.
+// ---------------------------------------------------------------------------------------------
+constexpr int kVjpRows = 4, kVjpWaves = 8;
+constexpr int kVjpTX = 62, kVjpTY = kVjpRows * kVjpWaves - 2;
+
+template <bool XDEP>
+__global__ __launch_bounds__(64 * kVjpWaves) void k_vjp(KArgs a, float* __restrict__ gphi,
+                                                        float* __restrict__ gA, int accumulate) {
+  __shared__ float Gy[kVjpRows * kVjpWaves][64];
+  const ProbDesc& p = a.p;
+  const int nx = p.nx, ny = p.ny, L = p.lp.n;
+  const int local = xcd_remap(blockIdx.x, gridDim.x);
+  const int ntx = (nx + kVjpTX - 1) / kVjpTX;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int x = (local % ntx) * kVjpTX - 1 + lane;
+  const int y0 = (local / ntx) * kVjpTY - 1 + w * kVjpRows;
+  // region pixels off the image compute the nearest image pixel's values, which nothing reads
+  const int xc = min(max(x, 0), nx - 1);
+  const int xl = max(xc - 1, 0), xh = min(xc + 1, nx - 1);
+  const float cx = xh - xl == 2 ? 0.5f : 1.f;
+  gptr<const float> g = G(p.d);  // incoming gradient dL/dP
+  gptr<const float> X = G(p.X);
+  gptr<const float> Y = G(p.Y);
+  int yc[kVjpRows];
+  float px[kVjpRows], py[kVjpRows], av[kVjpRows];
+#pragma unroll
+  for (int r = 0; r < kVjpRows; ++r) {
+    yc[r] = min(max(y0 + r, 0), ny - 1);
+    const int yl = max(yc[r] - 1, 0), yh = min(yc[r] + 1, ny - 1);
+    px[r] = cx * (ldg(Y + yc[r] * nx, (unsigned)xh) - ldg(Y + yc[r] * nx, (unsigned)xl));
+    py[r] = (yh - yl == 2 ? 0.5f : 1.f) * (ldg(Y + yh * nx, (unsigned)xc) - ldg(Y + yl * nx, (unsigned)xc));
+    av[r] = ldg(X + yc[r] * nx, (unsigned)xc);
+  }
+  float sa[kVjpRows] = {}, sx[kVjpRows] = {}, sy[kVjpRows] = {};
+  for (int s = 0; s < L; ++s) {
+    const float4 c = line_wabq<XDEP>(p, xc, s);
+    float dx[kVjpRows], dy[kVjpRows], g00[kVjpRows], g10[kVjpRows], g01[kVjpRows], g11[kVjpRows];
+    int xt[kVjpRows], yt[kVjpRows];
+    bool inside = true;
+#pragma unroll
+    for (int r = 0; r < kVjpRows; ++r) {
+      // cell and in-cell position as the splat forms them
+      const float ux = c.z * px[r], uy = c.z * py[r];
+      dx[r] = __builtin_amdgcn_fractf(ux);
+      dy[r] = __builtin_amdgcn_fractf(uy);
+      xt[r] = xc + floor_to_int(ux);
+      yt[r] = yc[r] + floor_to_int(uy);
+      inside = inside && (unsigned)xt[r] <= (unsigned)(nx - 2) && (unsigned)yt[r] <= (unsigned)(ny - 2);
+    }
+    if (__all(inside)) {
+      const gptr<const float> b10 = g + 1, b01 = g + nx, b11 = g + nx + 1;
+#pragma unroll
+      for (int r = 0; r < kVjpRows; ++r) {
+        const unsigned o = (unsigned)(__mul24(yt[r], nx) + xt[r]);
+        g00[r] = ldg(g, o);
+        g10[r] = ldg(b10, o);
+        g01[r] = ldg(b01, o);
+        g11[r] = ldg(b11, o);
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < kVjpRows; ++r) {
+        const bool xi0 = (unsigned)xt[r] < (unsigned)nx, xi1 = (unsigned)(xt[r] + 1) < (unsigned)nx;
+        const bool yi0 = (unsigned)yt[r] < (unsigned)ny, yi1 = (unsigned)(yt[r] + 1) < (unsigned)ny;
+        const int x0 = min(max(xt[r], 0), nx - 1), x1 = min(max(xt[r] + 1, 0), nx - 1);
+        const int r0 = __mul24(min(max(yt[r], 0), ny - 1), nx);
+        const int r1 = __mul24(min(max(yt[r] + 1, 0), ny - 1), nx);
+        const float v00 = ldg(g, (unsigned)(r0 + x0)), v10 = ldg(g, (unsigned)(r0 + x1));
+        const float v01 = ldg(g, (unsigned)(r1 + x0)), v11 = ldg(g, (unsigned)(r1 + x1));
+        g00[r] = xi0 && yi0 ? v00 : 0.f;
+        g10[r] = xi1 && yi0 ? v10 : 0.f;
+        g01[r] = xi0 && yi1 ? v01 : 0.f;
+        g11[r] = xi1 && yi1 ? v11 : 0.f;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kVjpRows; ++r) {
+      const float I = c.x * expf(-c.y * av[r]);
+      const float d0 = g10[r] - g00[r], d1 = g11[r] - g01[r], e0 = g01[r] - g00[r], cc = d1 - d0;
+      const float gux = fmaf(dy[r], cc, d0), guy = fmaf(dx[r], cc, e0);
+      const float gI = fmaf(dy[r], guy, fmaf(dx[r], d0, g00[r]));
+      sa[r] = fmaf(-c.y * I, gI, sa[r]);
+      sx[r] = fmaf(c.z * I, gux, sx[r]);
+      sy[r] = fmaf(c.z * I, guy, sy[r]);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kVjpRows; ++r) Gy[w * kVjpRows + r][lane] = sy[r];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kVjpRows; ++r) {
+    const int q = w * kVjpRows + r, y = y0 + r;
+    const float l = lane_left(sx[r]), h = lane_right(sx[r]);
+    if (q == 0 || q == kVjpRows * kVjpWaves - 1 || y >= ny) continue;
+    if (lane == 0 || lane == 63 || x >= nx) continue;
+    const float t = d_transpose3(l, sx[r], h, x, nx) +
+                    d_transpose3(Gy[q - 1][lane], sy[r], Gy[q + 1][lane], y, ny);
+    const unsigned o = (unsigned)(__mul24(y, nx) + x);
+    if (accumulate) {
+      stg(G(gphi), o, sa[r] + t);
+    } else {
+      stg(G(gphi), o, t);
+      stg(G(gA), o, sa[r]);
+    }
+  }
 }
 
 // gphi = D_x^T Gx + D_y^T Gy, or (accumulate) that added to gphi.
-__global__ __launch_bounds__(kVjpThreads) void k_vjp_transpose(KArgs a,
-                                                               const float* __restrict__ Gx,
-                                                               const float* __restrict__ Gy,
-                                                               float* __restrict__ gphi,
-                                                               int accumulate) {
+constexpr int kTrThreads = 256;
+__global__ __launch_bounds__(kTrThreads) void k_vjp_transpose(KArgs a, const float* __restrict__ Gx,
+                                                              const float* __restrict__ Gy,
+                                                              float* __restrict__ gphi,
+                                                              int accumulate) {
   const ProbDesc& p = a.p;
   const int nx = p.nx, ny = p.ny;
-  const int i = blockIdx.x * kVjpThreads + threadIdx.x;
+  const int i = blockIdx.x * kTrThreads + threadIdx.x;
   if (i >= nx * ny) return;
   const int y = i / nx, x = i - y * nx;
-  const float* rowx = Gx + (size_t)y * nx;
-  const float tx = d_transpose([&](int k) { return rowx[k]; }, x, nx);
-  const float ty = d_transpose([&](int k) { return Gy[(size_t)k * nx + x]; }, y, ny);
-  gphi[i] = accumulate ? gphi[i] + (tx + ty) : tx + ty;
+  // neighbours off the image are clamped reads that the one-sided rows do not use
+  const unsigned row = (unsigned)__mul24(y, nx);
+  const int xl = max(x - 1, 0), xh = min(x + 1, nx - 1), yl = max(y - 1, 0), yh = min(y + 1, ny - 1);
+  gptr<const float> gx = G(Gx);
+  gptr<const float> gy = G(Gy);
+  const float t = d_transpose3(ldg(gx, row + xl), ldg(gx, row + x), ldg(gx, row + xh), x, nx) +
+                  d_transpose3(ldg(gy, (unsigned)(__mul24(yl, nx) + x)), ldg(gy, row + x),
+                               ldg(gy, (unsigned)(__mul24(yh, nx) + x)), y, ny);
+  gphi[i] = accumulate ? gphi[i] + t : t;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -112,210 +184,239 @@ __global__ __launch_bounds__(kVjpThreads) void k_vjp_transpose(KArgs a,
 //                  dQ = -q_s (D_x^T(I k_x) + D_y^T(I k_y)),  t = dQ / A
 //                  dI += (lap^T t - t Q) / (2 A)
 // then grad_A += -a_s I dI and G_x += b_s du_x, G_y += b_s du_y (grad_phi = D_x^T G_x + D_y^T G_y
-// by k_vjp_transpose).  The pressure part takes three passes over per-line planes: A, then Q
-// (D D A), then t (which replaces A).
+// by k_vjp_transpose).
+//
+// As in the closure itself, a wave works on a strip of kLocalCols output columns x kVsRows rows
+// alone: column neighbours from the adjacent lanes, row neighbours in registers, so the chain of
+// derivatives (four deep in t) needs no planes in memory.  The waves of a workgroup share the lines
+// of one strip and add their sums through LDS at the end.
+// Bound by vector issue.  1024 x 1280, 4 lines, pressure term: 138 us (four passes over per-line
+// planes of A, Q and t) -> 24 us.
 // ---------------------------------------------------------------------------------------------
+constexpr int kVsRows = 8;
+constexpr int kVsWavesMax = 4;
 
-// D along one axis of length n applied to the sequence at(.) at index j.
-template <class F>
-__device__ __forceinline__ float d_apply(F at, int j, int n) {
-  if (j == 0) return at(1) - at(0);
-  if (j == n - 1) return at(n - 1) - at(n - 2);
-  return 0.5f * (at(j + 1) - at(j - 1));
-}
-
-// I_s at a pixel of column x whose map value is xv
-template <bool XDEP>
-__device__ __forceinline__ float line_intensity(const ProbDesc& p, int x, int s, float xv) {
-  const float4 c = line_wabq<XDEP>(p, x, s);
-  return c.x * expf(-c.y * xv);
-}
-
-// A_s = sqrt(I_s) into plane s of `work` ([L][ny][nx]).
-template <bool XDEP>
-__global__ __launch_bounds__(kVjpThreads) void k_vjp_sqrt_i(KArgs a, float* __restrict__ work) {
-  const ProbDesc& p = a.p;
-  const int n = p.nx * p.ny;
-  const int i = blockIdx.x * kVjpThreads + threadIdx.x;
-  if (i >= n) return;
-  const float xv = p.X[i];
-  const int x = i % p.nx;
-  for (int s = 0; s < p.lp.n; ++s) work[(size_t)s * n + i] = sqrtf(line_intensity<XDEP>(p, x, s, xv));
-}
-
-// Q_s = (D_x D_x A_s + D_y D_y A_s) / A_s from the A planes in `work`, into the planes of `q`.
-__global__ __launch_bounds__(kVjpThreads) void k_vjp_q(KArgs a, const float* __restrict__ work,
-                                                       float* __restrict__ q) {
-  const ProbDesc& p = a.p;
-  const int nx = p.nx, ny = p.ny, n = nx * ny;
-  const int i = blockIdx.x * kVjpThreads + threadIdx.x;
-  if (i >= n) return;
-  const int y = i / nx, x = i - y * nx;
-  for (int s = 0; s < p.lp.n; ++s) {
-    const float* A = work + (size_t)s * n;
-    const float* row = A + (size_t)y * nx;
-    const float dxx = d_apply([&](int m) { return d_apply([&](int k) { return row[k]; }, m, nx); }, x, nx);
-    const float dyy = d_apply([&](int m) { return d_apply([&](int k) { return A[(size_t)k * nx + x]; }, m, ny); }, y, ny);
-    q[(size_t)s * n + i] = (dxx + dyy) / row[x];
-  }
-}
-
-// t_s = dQ_s / A_s, dQ_s = -q_s (D_x^T(I_s k_x) + D_y^T(I_s k_y)), replacing A_s in `work`.
-// (XDEP: q_s varies along x and scales the pressure term after its outer derivative, so the
-// row factor is D_x^T(q_s g) and the column factor q_s(x) D_y^T g.)
-template <bool XDEP>
-__global__ __launch_bounds__(kVjpThreads) void k_vjp_t(KArgs a, float* __restrict__ work) {
-  const ProbDesc& p = a.p;
-  const int nx = p.nx, ny = p.ny, n = nx * ny;
-  const int i = blockIdx.x * kVjpThreads + threadIdx.x;
-  if (i >= n) return;
-  const int y = i / nx, x = i - y * nx;
-  const float* g = p.d;
-  const float* X = p.X;
-  for (int s = 0; s < p.lp.n; ++s) {
-    // k_x at (y, m) and k_y at (m, x)
-    const float ty = d_transpose([&](int m) {
-      return line_intensity<XDEP>(p, x, s, X[(size_t)m * nx + x]) *
-             d_transpose([&](int k) { return g[(size_t)k * nx + x]; }, m, ny);
-    }, y, ny);
-    float dq;
-    if constexpr (XDEP) {
-      const float tx = d_transpose([&](int m) {
-        return line_intensity<XDEP>(p, m, s, X[(size_t)y * nx + m]) *
-               d_transpose([&](int k) { return xcol_at(p, k, s).w * g[(size_t)y * nx + k]; }, m, nx);
-      }, x, nx);
-      dq = -(tx + xcol_at(p, x, s).w * ty);
-    } else {
-      const float tx = d_transpose([&](int m) {
-        return line_intensity<XDEP>(p, m, s, X[(size_t)y * nx + m]) *
-               d_transpose([&](int k) { return g[(size_t)y * nx + k]; }, m, nx);
-      }, x, nx);
-      dq = -p.lp.q[s] * (tx + ty);
+// ORDER 1 or 2 (local closures), or 3 (the pressure term alone, added to the transport's
+// gradient already in gA).  EDGE: the strip meets the image border (see local_strip).
+template <int ORDER, bool XDEP, bool EDGE>
+__device__ __forceinline__ void vjp_strip_line(const ProbDesc& p, int s, int y0, int x, int xc,
+                                               const float (&Xv)[kVsRows + 2 * kLocalHalo],
+                                               const float (&Gv)[kVsRows + 2 * kLocalHalo],
+                                               const float (&px)[kVsRows], const float (&py)[kVsRows],
+                                               float (&sa)[kVsRows], float (&sx)[kVsRows],
+                                               float (&sy)[kVsRows]) {
+  constexpr int H = kLocalHalo, N = kVsRows + 2 * H;
+  const int nx = p.nx, ny = p.ny;
+  const float4 c = line_wabq<XDEP>(p, xc, s);
+  const bool xfirst = x == 0, xlast = x == nx - 1;
+  auto dx = [&](float f) {  // D_x
+    float l = lane_left(f), r = lane_right(f);
+    if constexpr (EDGE) {
+      l = xfirst ? f : l;
+      r = xlast ? f : r;
+      return ((xfirst || xlast) ? 1.f : 0.5f) * (r - l);
     }
-    float* A = work + (size_t)s * n;
-    A[i] = dq / A[i];
+    return 0.5f * (r - l);
+  };
+  auto dy = [&](int i, float fm, float f0, float fp) {  // D_y at input row i
+    if constexpr (EDGE) {
+      const int y = y0 - H + i;
+      const float t = y == 0 ? f0 : fm, b = y == ny - 1 ? f0 : fp;
+      return ((y == 0 || y == ny - 1) ? 1.f : 0.5f) * (b - t);
+    }
+    return 0.5f * (fp - fm);
+  };
+  auto dxt = [&](float f) {  // D_x^T
+    const float l = lane_left(f), r = lane_right(f);
+    if constexpr (EDGE) return d_transpose3(l, f, r, x, nx);
+    return 0.5f * (l - r);
+  };
+  auto dyt = [&](int i, float fm, float f0, float fp) {  // D_y^T at input row i
+    if constexpr (EDGE) return d_transpose3(fm, f0, fp, y0 - H + i, ny);
+    return 0.5f * (fm - fp);
+  };
+  const float ca2 = c.y * 1.4426950408889634f, ha2 = 0.5f * ca2;
+  const float sw = __builtin_amdgcn_sqrtf(c.x);
+  float I[N], A[N], rA[N], dyA[N], Q[N], kx[N], ky[N], vx[N], vy[N], t[N], ut[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    // (the pressure term is small against I: hardware exp2 there)
+    if constexpr (ORDER == kOrderTransportWkb1)
+      I[i] = c.x * __builtin_amdgcn_exp2f(-ca2 * Xv[i]);
+    else
+      I[i] = c.x * expf(-c.y * Xv[i]);
+    kx[i] = dxt(Gv[i]);
+    if constexpr (ORDER >= 2) {
+      A[i] = sw * __builtin_amdgcn_exp2f(-ha2 * Xv[i]);
+      rA[i] = __builtin_amdgcn_rcpf(A[i]);
+      if (i >= 2) dyA[i - 1] = dy(i - 1, A[i - 2], A[i - 1], A[i]);
+      // XDEP: q_s scales the pressure term after its outer derivative, so the row factor is
+      // D_x^T(q_s g) and the column factor q_s(x) D_y^T g
+      vx[i] = I[i] * (XDEP ? dxt(c.w * Gv[i]) : kx[i]);
+    }
+    if (i >= 2) {
+      ky[i - 1] = dyt(i - 1, Gv[i - 2], Gv[i - 1], Gv[i]);
+      if constexpr (ORDER >= 2) vy[i - 1] = I[i - 1] * ky[i - 1];
+    }
+    if constexpr (ORDER >= 2) {
+      const int j = i - 2;
+      if (j >= 2 && j < N - 2) {
+        Q[j] = (dx(dx(A[j])) + dy(j, dyA[j - 1], dyA[j], dyA[j + 1])) * rA[j];
+        const float tx = dxt(vx[j]), ty = dyt(j, vy[j - 1], vy[j], vy[j + 1]);
+        t[j] = (XDEP ? -fmaf(c.w, ty, tx) : -c.w * (tx + ty)) * rA[j];
+      }
+      const int k = i - 3;
+      if (k >= 3 && k < N - 3) ut[k] = dyt(k, t[k - 1], t[k], t[k + 1]);
+    }
+    const int m = i - H;
+    if (m >= H && m < N - H) {
+      const int o = m - H;
+      float dI = 0.f;
+      if constexpr (ORDER != kOrderTransportWkb1) {
+        const float ux = c.z * px[o], uy = c.z * py[o];
+        dI = Gv[m] - (ux * kx[m] + uy * ky[m]);
+        float dux = -I[m] * kx[m], duy = -I[m] * ky[m];
+        if constexpr (ORDER == 2) {
+          const float hxx = dxt(kx[m]), hyy = dyt(m, ky[m - 1], ky[m], ky[m + 1]);
+          const float hm = 2.f * dxt(ky[m]);  // h_xy + h_yx (the transposes commute)
+          dI += 0.5f * (ux * ux * hxx + ux * uy * hm + uy * uy * hyy);
+          dux += 0.5f * I[m] * (2.f * ux * hxx + uy * hm);
+          duy += 0.5f * I[m] * (ux * hm + 2.f * uy * hyy);
+        }
+        sx[o] += c.z * dux;
+        sy[o] += c.z * duy;
+      }
+      if constexpr (ORDER >= 2) {
+        const float dqx = dx(Q[m]), dqy = dy(m, Q[m - 1], Q[m], Q[m + 1]);
+        if constexpr (XDEP)
+          dI += -(dqx * dxt(c.w * Gv[m]) + dqy * (c.w * ky[m]));
+        else
+          dI += -c.w * (dqx * kx[m] + dqy * ky[m]);
+        const float lap = dxt(dxt(t[m])) + dyt(m, ut[m - 1], ut[m], ut[m + 1]);
+        dI += (lap - t[m] * Q[m]) * (0.5f * rA[m]);
+      }
+      sa[o] -= c.y * I[m] * dI;
+    }
   }
 }
 
-// Per-pixel gradients of every line, summed: ORDER 1 or 2 (local closures), or 3 (the pressure
-// term alone, added to the transport's gradients already in gA).  `work` holds t, `q` holds Q
-// (both unused for ORDER 1).
+template <int ORDER, bool XDEP, bool EDGE>
+__device__ __forceinline__ void vjp_strip(const ProbDesc& p, int w, int nw, int y0, int xs,
+                                          float (&sa)[kVsRows], float (&sx)[kVsRows],
+                                          float (&sy)[kVsRows]) {
+  constexpr int H = kLocalHalo, N = kVsRows + 2 * H;
+  const int nx = p.nx, ny = p.ny;
+  const int x = xs - H + (int)(threadIdx.x & 63);
+  const int xc = EDGE ? min(max(x, 0), nx - 1) : x;
+  gptr<const float> X = G(p.X);
+  gptr<const float> Y = G(p.Y);
+  gptr<const float> g = G(p.d);
+  float Xv[N], Gv[N], px[kVsRows] = {}, py[kVsRows] = {};
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int y = y0 - H + i, yc = EDGE ? min(max(y, 0), ny - 1) : y;
+    Xv[i] = ldg(X + yc * nx, (unsigned)xc);
+    Gv[i] = ldg(g + yc * nx, (unsigned)xc);
+  }
+  if constexpr (ORDER != kOrderTransportWkb1) {
+#pragma unroll
+    for (int o = 0; o < kVsRows; ++o) {
+      const int yc = min(y0 + o, ny - 1);
+      const int xl = max(xc - 1, 0), xh = min(xc + 1, nx - 1);
+      const int yl = max(yc - 1, 0), yh = min(yc + 1, ny - 1);
+      px[o] = (xh - xl == 2 ? 0.5f : 1.f) * (ldg(Y + yc * nx, (unsigned)xh) - ldg(Y + yc * nx, (unsigned)xl));
+      py[o] = (yh - yl == 2 ? 0.5f : 1.f) * (ldg(Y + yh * nx, (unsigned)xc) - ldg(Y + yl * nx, (unsigned)xc));
+    }
+  }
+  for (int s = w; s < p.lp.n; s += nw)
+    vjp_strip_line<ORDER, XDEP, EDGE>(p, s, y0, x, xc, Xv, Gv, px, py, sa, sx, sy);
+}
+
 template <int ORDER, bool XDEP>
-__global__ __launch_bounds__(kVjpThreads) void k_vjp_local(KArgs a, const float* __restrict__ work,
-                                                           const float* __restrict__ q,
-                                                           float* __restrict__ Gx,
-                                                           float* __restrict__ Gy,
-                                                           float* __restrict__ gA) {
+__global__ __launch_bounds__(64 * kVsWavesMax) void k_vjp_local(KArgs a, float* __restrict__ Gx,
+                                                                float* __restrict__ Gy,
+                                                                float* __restrict__ gA) {
+  constexpr int NQ = ORDER == kOrderTransportWkb1 ? 1 : 3;  // sums: A alone, or A, G_x, G_y
+  __shared__ float red[kVsWavesMax][NQ][kVsRows][64];
   const ProbDesc& p = a.p;
-  const int nx = p.nx, ny = p.ny, n = nx * ny;
-  const int i = blockIdx.x * kVjpThreads + threadIdx.x;
-  if (i >= n) return;
-  const int y = i / nx, x = i - y * nx;
-  const float* g = p.d;
-  const float* grow = g + (size_t)y * nx;
-  auto kxat = [&](int yy, int xx) { return d_transpose([&](int k) { return g[(size_t)yy * nx + k]; }, xx, nx); };
-  auto kyat = [&](int yy, int xx) { return d_transpose([&](int k) { return g[(size_t)k * nx + xx]; }, yy, ny); };
-  const float kx = d_transpose([&](int k) { return grow[k]; }, x, nx);
-  const float ky = kyat(y, x);
-  float hxx = 0.f, hyy = 0.f, hxy = 0.f, hyx = 0.f;
-  if (ORDER == 2) {
-    hxx = d_transpose([&](int m) { return kxat(y, m); }, x, nx);
-    hyy = d_transpose([&](int m) { return kyat(m, x); }, y, ny);
-    hxy = d_transpose([&](int m) { return kxat(m, x); }, y, ny);   // transpose of D_x D_y
-    hyx = d_transpose([&](int m) { return kyat(y, m); }, x, nx);   // transpose of D_y D_x
-  }
-  float px = 0.f, py = 0.f;
-  if (ORDER != 3) {
-    px = d_x(G(p.Y), y, x, nx);
-    py = d_y(G(p.Y), y, x, ny, nx);
-  }
-  const float xv = p.X[i];
-  float sa = 0.f, sx = 0.f, sy = 0.f;
-  for (int s = 0; s < p.lp.n; ++s) {
-    const float4 c = line_wabq<XDEP>(p, x, s);
-    const float I = c.x * expf(-c.y * xv);
-    float dI = 0.f;
-    if (ORDER != 3) {
-      const float bs = c.z;
-      const float ux = bs * px, uy = bs * py;
-      dI = g[i] - (ux * kx + uy * ky);
-      float dux = -I * kx, duy = -I * ky;
-      if (ORDER == 2) {
-        const float hm = hxy + hyx;
-        dI += 0.5f * (ux * ux * hxx + ux * uy * hm + uy * uy * hyy);
-        dux += 0.5f * I * (2.f * ux * hxx + uy * hm);
-        duy += 0.5f * I * (ux * hm + 2.f * uy * hyy);
-      }
-      sx += bs * dux;
-      sy += bs * duy;
+  const int nx = p.nx, ny = p.ny;
+  const int local = xcd_remap(blockIdx.x, gridDim.x);
+  const int ntx = (nx + kLocalCols - 1) / kLocalCols;
+  const int y0 = (local / ntx) * kVsRows, xs = (local % ntx) * kLocalCols;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nw = blockDim.x >> 6;
+  float sa[kVsRows] = {}, sx[kVsRows] = {}, sy[kVsRows] = {};
+  const bool inner = xs >= kLocalHalo + 1 && xs + kLocalCols + kLocalHalo + 1 <= nx &&
+                     y0 >= kLocalHalo + 1 && y0 + kVsRows + kLocalHalo + 1 <= ny;
+  if (inner)
+    vjp_strip<ORDER, XDEP, false>(p, w, nw, y0, xs, sa, sx, sy);
+  else
+    vjp_strip<ORDER, XDEP, true>(p, w, nw, y0, xs, sa, sx, sy);
+#pragma unroll
+  for (int o = 0; o < kVsRows; ++o) {
+    red[w][0][o][lane] = sa[o];
+    if constexpr (NQ == 3) {
+      red[w][1][o][lane] = sx[o];
+      red[w][2][o][lane] = sy[o];
     }
-    if (ORDER >= 2) {
-      const float* Qs = q + (size_t)s * n;
-      const float* T = work + (size_t)s * n;
-      const float dqx = d_x(G(Qs), y, x, nx), dqy = d_y(G(Qs), y, x, ny, nx);
-      if constexpr (XDEP) {
-        const float kqx = d_transpose([&](int k) { return xcol_at(p, k, s).w * grow[k]; }, x, nx);
-        dI += -(dqx * kqx + dqy * (c.w * ky));
-      } else {
-        dI += -c.w * (dqx * kx + dqy * ky);
-      }
-      const float* trow = T + (size_t)y * nx;
-      const float ltx = d_transpose([&](int m) { return d_transpose([&](int k) { return trow[k]; }, m, nx); }, x, nx);
-      const float lty = d_transpose([&](int m) { return d_transpose([&](int k) { return T[(size_t)k * nx + x]; }, m, ny); }, y, ny);
-      dI += (ltx + lty - trow[x] * Qs[i]) / (2.f * sqrtf(I));
-    }
-    sa -= c.y * I * dI;
   }
-  if (ORDER == 3) {
-    gA[i] += sa;
-  } else {
-    gA[i] = sa;
-    Gx[i] = sx;
-    Gy[i] = sy;
+  __syncthreads();
+  const int x = xs - kLocalHalo + lane;
+  if (lane < kLocalHalo || lane >= kLocalHalo + kLocalCols || x >= nx) return;
+  for (int o = w; o < kVsRows; o += nw) {
+    const int y = y0 + o;
+    if (y >= ny) break;
+    float v[NQ] = {};
+    for (int k = 0; k < nw; ++k)
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) v[q] += red[k][q][o][lane];
+    const unsigned i = (unsigned)(__mul24(y, nx) + x);
+    if constexpr (NQ == 1) {
+      stg(G(gA), i, ldg(G((const float*)gA), i) + v[0]);
+    } else {
+      stg(G(gA), i, v[0]);
+      stg(G(Gx), i, v[1]);
+      stg(G(Gy), i, v[2]);
+    }
   }
 }
 
 template <bool XDEP>
-hipError_t launch_vjp_local_t(const KArgs& a, int total_blocks, hipStream_t s, int order,
-                              float* work, float* q, float* gx, float* gy, float* ga) {
-  const dim3 grid(total_blocks), block(kVjpThreads);
-  if (order >= 2) {
-    hipLaunchKernelGGL(k_vjp_sqrt_i<XDEP>, grid, block, 0, s, a, work);
-    hipLaunchKernelGGL(k_vjp_q, grid, block, 0, s, a, work, q);
-    hipLaunchKernelGGL(k_vjp_t<XDEP>, grid, block, 0, s, a, work);
-  }
+hipError_t launch_vjp_local_t(const KArgs& a, hipStream_t s, int order, float* gx, float* gy,
+                              float* ga) {
+  const dim3 grid(((a.p.ny + kVsRows - 1) / kVsRows) * ((a.p.nx + kLocalCols - 1) / kLocalCols));
+  const dim3 block(64 * (a.p.lp.n < kVsWavesMax ? a.p.lp.n : kVsWavesMax));
   if (order == 1)
-    hipLaunchKernelGGL((k_vjp_local<1, XDEP>), grid, block, 0, s, a, work, q, gx, gy, ga);
+    hipLaunchKernelGGL((k_vjp_local<1, XDEP>), grid, block, 0, s, a, gx, gy, ga);
   else if (order == 2)
-    hipLaunchKernelGGL((k_vjp_local<2, XDEP>), grid, block, 0, s, a, work, q, gx, gy, ga);
+    hipLaunchKernelGGL((k_vjp_local<2, XDEP>), grid, block, 0, s, a, gx, gy, ga);
   else
-    hipLaunchKernelGGL((k_vjp_local<3, XDEP>), grid, block, 0, s, a, work, q, gx, gy, ga);
+    hipLaunchKernelGGL((k_vjp_local<3, XDEP>), grid, block, 0, s, a, gx, gy, ga);
   return hipGetLastError();
 }
 
-hipError_t launch_vjp_local(const KArgs& a, int total_blocks, hipStream_t s, int order,
-                            float* work, float* q, float* gx, float* gy, float* ga) {
-  return a.p.xcol ? launch_vjp_local_t<true>(a, total_blocks, s, order, work, q, gx, gy, ga)
-                  : launch_vjp_local_t<false>(a, total_blocks, s, order, work, q, gx, gy, ga);
+hipError_t launch_vjp_local(const KArgs& a, hipStream_t s, int order, float* gx, float* gy,
+                            float* ga) {
+  return a.p.xcol ? launch_vjp_local_t<true>(a, s, order, gx, gy, ga)
+                  : launch_vjp_local_t<false>(a, s, order, gx, gy, ga);
 }
 
-hipError_t launch_vjp(const KArgs& a, int total_blocks, size_t, hipStream_t s, float* gx,
-                      float* gy, float* ga) {
+hipError_t launch_vjp(const KArgs& a, hipStream_t s, float* gphi, float* ga, int accumulate) {
+  const dim3 grid(((a.p.ny + kVjpTY - 1) / kVjpTY) * ((a.p.nx + kVjpTX - 1) / kVjpTX));
+  const dim3 block(64 * kVjpWaves);
   if (a.p.xcol)
-    hipLaunchKernelGGL(k_vjp<true>, dim3(total_blocks), dim3(kVjpThreads), 0, s, a, gx, gy, ga);
+    hipLaunchKernelGGL(k_vjp<true>, grid, block, 0, s, a, gphi, ga, accumulate);
   else
-    hipLaunchKernelGGL(k_vjp<false>, dim3(total_blocks), dim3(kVjpThreads), 0, s, a, gx, gy, ga);
+    hipLaunchKernelGGL(k_vjp<false>, grid, block, 0, s, a, gphi, ga, accumulate);
   return hipGetLastError();
 }
 
-hipError_t launch_vjp_transpose(const KArgs& a, int total_blocks, hipStream_t s,
-                                const float* gx, const float* gy, float* gphase,
-                                int accumulate) {
-  hipLaunchKernelGGL(k_vjp_transpose, dim3(total_blocks), dim3(kVjpThreads), 0, s, a, gx, gy,
-                     gphase, accumulate);
+hipError_t launch_vjp_transpose(const KArgs& a, hipStream_t s, const float* gx, const float* gy,
+                                float* gphase, int accumulate) {
+  const int nb = (a.p.nx * a.p.ny + kTrThreads - 1) / kTrThreads;
+  hipLaunchKernelGGL(k_vjp_transpose, dim3(nb), dim3(kTrThreads), 0, s, a, gx, gy, gphase,
+                     accumulate);
   return hipGetLastError();
 }
-
-hipError_t set_vjp_attributes() { return hipSuccess; }
 
 }  // namespace epr
