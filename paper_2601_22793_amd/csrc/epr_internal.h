@@ -212,6 +212,12 @@ inline size_t lds_rowinv(const ProbDesc& p) {
   return sizeof(float2) * ((size_t)p.nblk * kColBlock * kRows + (size_t)kRows * lds_rows(p.nx / 2) +
                            tw_half(p.nx / 2));
 }
+// (row inverse with groups: tiles and transform buffer per group, one table)
+inline size_t lds_rowinv_groups(const ProbDesc& p, int groups) {
+  return sizeof(float2) * (groups * ((size_t)p.nblk * kColBlock * kRows + (size_t)kRows * lds_rows(p.nx / 2)) +
+                           tw_half(p.nx / 2));
+}
+constexpr int kRowGroupBlocks = 256;  // most row blocks of a row inverse that takes several lines at once
 // Threads of the spectral kernels for a problem: 512 up to 2048 x 2048, 1024 beyond.
 inline int spectral_threads(const ProbDesc& p) { return (p.nx <= 2048 && p.ny <= 2048) ? 512 : 1024; }
 // Longest column of the 1024-thread class's mid column-pass instance (2160-row detectors): built

@@ -85,6 +85,14 @@ __device__ __forceinline__ TwTable load_twiddles(int off, const FftPlan& plan, i
   return tt;
 }
 
+// Thread index within the NT threads that transform a buffer: the workgroup's, or those of one of
+// several groups of NT threads, each with a buffer of its own, that run the stages in step.
+template <int NT>
+__device__ __forceinline__ int group_thread() {
+  static_assert((NT & (NT - 1)) == 0, "a power of two");
+  return (int)(threadIdx.x & (NT - 1));
+}
+
 // Butterflies of radix R a thread holds in a stage of EMAX elements.  Radices 12 and 15 hold one
 // (30 complex values for two would double the registers of every kernel that has the stage):
 // the plans take them only where COUNT N / R <= NT (kernel_radices).
@@ -377,7 +385,7 @@ __device__ __forceinline__ void fft_stage(int boff, int n_rt, int p_rt, float in
   constexpr bool kOutStep = NC > 0 && PC > 0 && is_pow2(NC) && is_pow2(R) && is_pow2(PC);
 #pragma unroll
   for (int k = 0; k < BPT; ++k) {
-    const int b = threadIdx.x + k * NT;
+    const int b = group_thread<NT>() + k * NT;
     if (b < total) {
       const int i = b / COUNT;
       const int c = b - i * COUNT;
@@ -412,7 +420,7 @@ __device__ __forceinline__ void fft_stage(int boff, int n_rt, int p_rt, float in
     // natural order (element e of sequence c at e COUNT + c), with no LDS pass
 #pragma unroll
     for (int k = 0; k < BPT; ++k) {
-      const int b = threadIdx.x + k * NT;
+      const int b = group_thread<NT>() + k * NT;
       if (b < total) {
         const int c = b % COUNT;
 #pragma unroll
@@ -425,7 +433,7 @@ __device__ __forceinline__ void fft_stage(int boff, int n_rt, int p_rt, float in
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < BPT; ++k) {
-    const int b = threadIdx.x + k * NT;
+    const int b = group_thread<NT>() + k * NT;
     if (b < total) {
       const int c = b % COUNT;
       if constexpr (kOutStep) {
@@ -607,7 +615,7 @@ __device__ __forceinline__ void fft_fused_filter_stage(int boff, int n_rt, TwTab
   float2 u[BPT][R];
 #pragma unroll
   for (int k = 0; k < BPT; ++k) {
-    const int b = threadIdx.x + k * NT;
+    const int b = group_thread<NT>() + k * NT;
     if (b < total) {
       const int i = b / COUNT;
       const int c = b - i * COUNT;
@@ -636,7 +644,7 @@ __device__ __forceinline__ void fft_fused_filter_stage(int boff, int n_rt, TwTab
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < BPT; ++k) {
-    const int b = threadIdx.x + k * NT;
+    const int b = group_thread<NT>() + k * NT;
     if (b < total) {
       const int i = b / COUNT;
       const int c = b - i * COUNT;

@@ -22,7 +22,8 @@ __device__ __forceinline__ void fetch_row_tiles(gptr<const float2> sp, float2* d
                                                 int ny, int y0) {
   // 16-byte chunk q of the block: tile blk = q / 8, row r = (q / 2) % 4, columns 2 (q % 2) + {0,1}
   const int nq = nblk * 8;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int tid = group_thread<NT>(), lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   float4* d4 = reinterpret_cast<float4*>(dst);
   for (int base = wave * 64; base < nq; base += NT) {
     const int q = base + lane;
@@ -35,28 +36,31 @@ __device__ __forceinline__ void fetch_row_tiles(gptr<const float2> sp, float2* d
   }
 }
 
+// GR: lines transformed at once, by groups of NT threads (GR NT threads a workgroup).
 // XDEP: x-dependent spectrum, the update and projection constants are read per column.
 // BLK (with XDEP): block-wise preconditioner.  Each line has p.nbp filtered spectra, one per
 // preconditioner block b (block 0 at p.spec, block b >= 1 in p.spec_blk); the row
 // inverse transforms each of them and blends them per column with the interpolation weights
 // lambda_b(x) (p.xblk[x] = {b0, t}: lambda_b0 = 1 - t, lambda_(b0+1) = t, 0 otherwise) before
 // the update.
-template <int NT, bool SOLVE, bool XDEP, bool BLK = false>
+template <int NT, int GR, bool SOLVE, bool XDEP, bool BLK = false>
 __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
   using SC = SizeClass<NT>;
   extern __shared__ float2 buf[];
   const int nx = p.nx, ny = p.ny, M = nx >> 1;
   const int y0 = local * kRows;
   const int L = p.lp.n;
-  const int tid = threadIdx.x;
+  const int tid = group_thread<NT>();
+  const int grp = GR > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NT) : 0;
   const int nin = p.nblk * kColBlock * kRows;  // complex values of one line's tiles
   const size_t line_elems = (size_t)p.nblk * ny * kColBlock;
-  float2* raw = buf;        // the line's tiles as copied: [block][row][column]
-  float2* F = buf + nin;    // transform buffer
-  const TwTable tw = load_twiddles(nin + kRows * lds_rows(M), p.row, tid, NT);
+  const int region = nin + kRows * lds_rows(M);  // LDS of one group
+  float2* raw = buf + grp * region;  // the line's tiles as copied: [block][row][column]
+  float2* F = raw + nin;             // transform buffer
+  const TwTable tw = load_twiddles(GR * region, p.row, threadIdx.x, NT * GR);
   const float2 w1 = G(p.row_tw)[1];
   gptr<const float2> spec = G((const float2*)p.spec);
-  fetch_row_tiles<NT>(spec, raw, p.nblk, ny, y0);
+  fetch_row_tiles<NT>(spec + min(grp, L - 1) * line_elems, raw, p.nblk, ny, y0);
 
   // the thread's pixels: row r, column x = tid + j NT (k = r * kPerRow + j)
   constexpr int kPerRow = SC::kMaxNx / NT;
@@ -97,8 +101,10 @@ __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
 #pragma unroll
   for (int k = 0; k < (BLK ? SC::kPix : 1); ++k) dacc[k] = 0.f;
 
-  for (int un = 0; un < nunit; ++un) {
-    const int s = BLK ? un / nb : un;
+  // (a group without a line in the last round transforms line L - 1 again, for nothing)
+  for (int u0 = 0; u0 < nunit; u0 += GR) {
+    const int un = u0 + grp;
+    const int s = BLK ? un / nb : min(un, L - 1);
     const int bk = BLK ? un - s * nb : 0;
     __builtin_amdgcn_s_waitcnt(0);  // this wave's copies of unit un have landed
     __syncthreads();                // ... and everyone's; unit un-1 is no longer read
@@ -130,12 +136,13 @@ __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
       }
     }
     __syncthreads();  // the tiles are consumed: unit un+1 streams in during the transform
-    if (un + 1 < nunit) {
-      const int s1 = BLK ? (un + 1) / nb : un + 1, b1 = BLK ? (un + 1) - s1 * nb : 0;
+    if (u0 + GR < nunit) {
+      const int s1 = BLK ? (un + 1) / nb : min(un + GR, L - 1), b1 = BLK ? (un + 1) - s1 * nb : 0;
       gptr<const float2> sb = b1 == 0 ? spec : G((const float2*)p.spec_blk) + (size_t)(b1 - 1) * p.spec_set;
       fetch_row_tiles<NT>(sb + (size_t)s1 * line_elems, raw, p.nblk, ny, y0);
     }
-    fft_lds<kRows, NT, SC::kRowEmax, SOLVE ? (BLK ? 5 : 3) : 4>(nin, p.row, tw);
+    fft_lds<kRows, NT, SC::kRowEmax, SOLVE ? (BLK ? 5 : 3) : 4>(grp * region + nin, p.row, tw);
+    if (GR > 1 && un >= nunit) continue;
 
     const float* fb = reinterpret_cast<const float*>(F);
     if constexpr (BLK) {
@@ -225,13 +232,32 @@ __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
   if constexpr (SOLVE) {
     const float inv_den = p.lp.inv_den, pc = p.lp.phase_coef;
     bool bad = !(fabsf(chk) <= 3.40282347e38f);
+    if constexpr (GR > 1) {
+      // the groups' projection sums meet in LDS (each in its own region, [row][column]), in the
+      // order of the groups; group g finishes the rows r with r mod GR = g
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < SC::kPix; ++k) {
+        const int r = k / kPerRow, x = tid + (k % kPerRow) * NT;
+        if (live[k % kPerRow] && x < nx) reinterpret_cast<float*>(raw)[r * nx + x] = acc[k];
+      }
+      __syncthreads();
+    }
 #pragma unroll
     for (int k = 0; k < SC::kPix; ++k) {
       const int r = k / kPerRow, x = tid + (k % kPerRow) * NT, y = y0 + r;
+      if (GR > 1 && r % GR != grp) continue;
       if (live[k % kPerRow] && x < nx && y < ny) {
+        float sum = acc[k];
+        if constexpr (GR > 1) {
+          sum = 0.f;
+#pragma unroll
+          for (int g = 0; g < GR; ++g)
+            sum += reinterpret_cast<const float*>(buf + g * region)[r * nx + x];
+        }
         float id = inv_den;
         if constexpr (XDEP) id = ldg(G(p.xden), (unsigned)x);
-        const float t = fmaf(-acc[k], id, thick ? 0.f : tv[k]);
+        const float t = fmaf(-sum, id, thick ? 0.f : tv[k]);
         bad = bad || !(fabsf(t) <= 3.40282347e38f);
         stg(G(p.tau), (unsigned)(__mul24(y, nx) + x), t);
         if (p.phase_out) stg(G(p.phase_out), (unsigned)(__mul24(y, nx) + x), pc * t);
@@ -246,24 +272,47 @@ __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
 template <bool B, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_rowinv(
     KArgs a, const ProbDesc* __restrict__ table) {
-  EPR_DISPATCH(B, a, table, xcd_remap(blockIdx.x, gridDim.x), (rowinv_body<NT, true, false>), 0);
+  EPR_DISPATCH(B, a, table, xcd_remap(blockIdx.x, gridDim.x), (rowinv_body<NT, 1, true, false>), 0);
 }
 template <bool B, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_rowinv_x(
     KArgs a, const ProbDesc* __restrict__ table) {
-  EPR_DISPATCH(B, a, table, xcd_remap(blockIdx.x, gridDim.x), (rowinv_body<NT, true, true>), 0);
+  EPR_DISPATCH(B, a, table, xcd_remap(blockIdx.x, gridDim.x), (rowinv_body<NT, 1, true, true>), 0);
 }
 // x-dependent spectrum with the block-wise preconditioner
 template <int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_rowinv_xb(
     KArgs a, const ProbDesc* __restrict__ table) {
   EPR_DISPATCH(false, a, table, xcd_remap(blockIdx.x, gridDim.x),
-               (rowinv_body<NT, true, true, true>), 0);
+               (rowinv_body<NT, 1, true, true, true>), 0);
 }
 template <bool B, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_rowinv_pre(
     KArgs a, const ProbDesc* __restrict__ table) {
-  EPR_DISPATCH(B, a, table, xcd_remap(blockIdx.x, gridDim.x), (rowinv_body<NT, false, false>), 0);
+  EPR_DISPATCH(B, a, table, xcd_remap(blockIdx.x, gridDim.x), (rowinv_body<NT, 1, false, false>), 0);
+}
+
+// GR lines of a row block at once (single problems): GR groups of NT threads, each with its own
+// LDS buffers, take the lines in turn.  A row block's lines are a serial chain of LDS transforms
+// and barriers, and a small image has few row blocks: 64 workgroups on 256 CUs at 256 rows.  (The
+// plans' radices fit any NT >= nx / 4: kRows (nx / 2) / 12 <= nx / 4.)
+template <int NT, int GR, bool SOLVE, bool XDEP>
+__global__ __launch_bounds__(NT * GR) __attribute__((amdgpu_waves_per_eu(4))) void k_rowinv_g(
+    KArgs a, const ProbDesc* __restrict__ table) {
+  EPR_DISPATCH(false, a, table, xcd_remap(blockIdx.x, gridDim.x),
+               (rowinv_body<NT, GR, SOLVE, XDEP>), 0);
+}
+
+template <int NT, int GR>
+void launch_rowinv_g(const KArgs& a, int total_blocks, hipStream_t s) {
+  const size_t lds = lds_rowinv_groups(a.p, GR);
+  const dim3 grid(total_blocks), block(NT * GR);
+  if (a.mode != kRowInvSolve)
+    hipLaunchKernelGGL((k_rowinv_g<NT, GR, false, false>), grid, block, lds, s, a, a.table);
+  else if (a.p.xcol)
+    hipLaunchKernelGGL((k_rowinv_g<NT, GR, true, true>), grid, block, lds, s, a, a.table);
+  else
+    hipLaunchKernelGGL((k_rowinv_g<NT, GR, true, false>), grid, block, lds, s, a, a.table);
 }
 
 // single-problem kernels (the block-wise row inverse)
@@ -277,6 +326,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 
 hipError_t launch_rowinv(const KArgs& a, int total_blocks, size_t lds, hipStream_t s, int nt) {
   const bool x = a.table ? a.xdep != 0 : a.p.xcol != nullptr;
+  // Several lines at once for a single problem of at most one row block per CU (a workgroup of
+  // groups fills one).  256 x 256, 10 lines: 30 -> 17 us; 1024 x 1024, 8 lines, x-dependent:
+  // 36 -> 27 us; 90 x 96, 4 lines, preconditioner: 13 -> 7 us.  With more row blocks, or two groups
+  // of 512 threads for wider rows, the CUs that hold two blocks run them one after the other and
+  // the pass gets slower (1215 x 1500, 4 lines: 34 -> 46 us).
+  if (!a.table && a.p.nbp == 0 && a.p.nx <= 1024 && a.p.lp.n > 1 && total_blocks <= kRowGroupBlocks) {
+    if (a.p.nx <= 512 && a.p.lp.n > 4)
+      launch_rowinv_g<128, 8>(a, total_blocks, s);
+    else if (a.p.lp.n > 2)
+      launch_rowinv_g<256, 4>(a, total_blocks, s);
+    else
+      launch_rowinv_g<256, 2>(a, total_blocks, s);
+    return hipGetLastError();
+  }
   if (a.mode == kRowInvSolve && !a.table && a.p.xcol && a.p.nbp > 0)
     EPR_LAUNCH_X(k_rowinv_xb, a, total_blocks, nt, lds, s);
   else if (a.mode == kRowInvSolve && x)
@@ -291,7 +354,13 @@ hipError_t launch_rowinv(const KArgs& a, int total_blocks, size_t lds, hipStream
 
 hipError_t set_rowinv_attributes() {
   const void* const fns[] = {EPR_SC_FNS(k_rowinv), EPR_SC_FNS(k_rowinv_pre), EPR_SC_FNS(k_rowinv_x),
-                             (const void*)k_rowinv_xb<512>, (const void*)k_rowinv_xb<1024>};
+                             (const void*)k_rowinv_xb<512>, (const void*)k_rowinv_xb<1024>,
+#define EPR_G_FNS(NT, GR)                                   \
+  (const void*)k_rowinv_g<NT, GR, true, false>,             \
+      (const void*)k_rowinv_g<NT, GR, true, true>,          \
+      (const void*)k_rowinv_g<NT, GR, false, false>
+                             EPR_G_FNS(128, 8), EPR_G_FNS(256, 4), EPR_G_FNS(256, 2)};
+#undef EPR_G_FNS
   return allow_dynamic_lds(fns);
 }
 
