@@ -123,7 +123,7 @@ def kernel_instance(stage, cls, batched, n_lines, row_lines):
     if stage in ("rowfft", "colfft", "rowinv"):
         return f"k_{stage}<{b}, {512 if cls == 0 else 1024}>"
     if stage == "splat":
-        nl = next(v for v in (1, 2, 4, 8, 16) if v >= n_lines)
+        nl = next(v for v in (1, 2, 3, 4, 5, 8, 10, 16) if v >= n_lines)
         return f"k_splat<{b}, {nl}>"
     return f"k_{stage}<{b}>"
 

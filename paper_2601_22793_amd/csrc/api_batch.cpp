@@ -255,6 +255,8 @@ int solve_batched_impl(epr_ctx* h, int32_t n, const epr_problem* problems,
         descs[i].xcol = reinterpret_cast<const float4*>(xb);
         descs[i].xden = reinterpret_cast<const float*>(xb + cb);
       }
+      descs[i].splat_tx = h->splat_tx;  // (the small tile is for single images)
+      descs[i].splat_ty = h->splat_ty;
       set_oversample(&descs[i], f);
       descs[i].X = q.thickness;
       descs[i].Y = q.thickness;
@@ -262,7 +264,7 @@ int solve_batched_impl(epr_ctx* h, int32_t n, const epr_problem* problems,
       descs[i].tau = q.thickness;
       descs[i].relax = (float)opts->relaxation;
       descs[i].status = static_cast<unsigned*>(h->status.ptr) + i;
-      apply_row_lines(h, &descs[i]);
+      apply_row_lines(h, &descs[i], false);
       // only the caller's problem 0 keeps its residual partials (the history records it)
       if (i != 0 || !(opts->flags & EPR_FLAG_RESIDUALS)) descs[i].resid = nullptr;
     }

@@ -44,7 +44,7 @@ int epr_solve(epr_handle h, const epr_geometry* geom, const epr_spectrum* spec,
   const bool want_resid = (opts->flags & EPR_FLAG_RESIDUALS) != 0;
   if (!want_resid) p.resid = nullptr;
   p.status = static_cast<unsigned*>(h->status.ptr);
-  apply_row_lines(h, &p);
+  apply_row_lines(h, &p, true);
   int model = opts->model;
   if (model == EPR_AUTO)
     CHECK(select_impl(h, *geom, *spec, *mat, intensity, EPR_AUTO_MAX_FRACTION, &model, nullptr, st));
@@ -113,7 +113,7 @@ int epr_solve_noalloc(epr_handle h, const epr_geometry* geom, const epr_spectrum
   const bool want_resid = (opts->flags & EPR_FLAG_RESIDUALS) != 0;
   if (!want_resid) p.resid = nullptr;
   p.status = static_cast<unsigned*>(h->status.ptr);
-  apply_row_lines(h, &p);
+  apply_row_lines(h, &p, true);
   // every launch enqueued directly (no graph, no timing events)
   const bool saved = h->timing;
   h->timing = false;
@@ -197,7 +197,7 @@ int epr_solve_xspec(epr_handle h, const epr_geometry* geom, const epr_spectrum* 
   set_oversample(&p, f);
   p.xcol = xcol;
   p.xden = den;
-  apply_row_lines(h, &p);
+  apply_row_lines(h, &p, true);
   const bool want_resid = (opts->flags & EPR_FLAG_RESIDUALS) != 0;
   if (!want_resid) p.resid = nullptr;
   p.status = static_cast<unsigned*>(h->status.ptr);

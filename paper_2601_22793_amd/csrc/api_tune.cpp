@@ -187,7 +187,7 @@ int epr_autotune(epr_handle h, int32_t n, const epr_problem* problems, const epr
     set_oversample(p, f);
     p->resid = nullptr;
     p->status = nullptr;
-    apply_row_lines(h, p);
+    apply_row_lines(h, p, true);
     return EPR_OK;
   };
 

@@ -39,6 +39,8 @@ __host__ __device__ inline int seg_band(int y, int ny) {
 constexpr int kSplatThreads = 512;
 constexpr int kSplatTileX = 64;  // default splat tile (columns x rows)
 constexpr int kSplatTileY = 32;
+constexpr int kSplatSmallX = 32; // tile of a single image with fewer default tiles than CUs
+constexpr int kSplatSmallY = 16;
 
 // One FFT length: radix sequence and twiddle table. tw[j * tw_stride] = exp(-2 pi i j / n).
 // The kernels copy the first tw_half(n) entries to LDS (the rest follow by W^(j+n/2) = -W^j).

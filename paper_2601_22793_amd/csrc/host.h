@@ -257,7 +257,7 @@ int upload_xtable(epr_ctx* h, const XTable& t, hipStream_t st, const float4** co
 int fill_desc(epr_ctx* h, const epr_geometry& g, const LineParams& lp, char* base, ProbDesc* p,
               const float2* row_tab = nullptr, const float2* col_tab = nullptr);
 void set_oversample(ProbDesc* p, int f);
-void apply_row_lines(const epr_ctx* h, ProbDesc* p);
+void apply_row_lines(const epr_ctx* h, ProbDesc* p, bool single_image);
 KArgs single(const ProbDesc& p, int mode);
 int launch_transport_lines(epr_ctx* h, const ProbDesc& p, hipStream_t st, int cls);
 int launch_predict_bin(epr_ctx* h, const ProbDesc& p, int model, hipStream_t st,

@@ -347,28 +347,32 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
   gptr<const float> X = G(p.X);
   gptr<const float> Y = G(p.Y);
 
-  // the default tile's detector data, read before the source loop that hides their latency
-  constexpr int kPre = kSplatTileX * kSplatTileY / kSplatThreads;
-  float dpre[kPre];
-  if (mode == kSplatSplit && TX == kSplatTileX && TY == kSplatTileY) {
-#pragma unroll
-    for (int k = 0; k < kPre; ++k) {
-      const int i = tid + k * kSplatThreads;
-      const int y = min(ty0 + i / kSplatTileX, ny - 1), x = min(tx0 + i % kSplatTileX, nx - 1);
-      dpre[k] = ldg(G((const float*)p.d), (unsigned)(__mul24(y, nx) + x));
-    }
-  }
-
   // The source loop and the read-back, specialised for the common case (every line of the
-  // bound in use, fixed-point accumulation, the default tile): no per-line tests are left in it.
+  // bound in use, fixed-point accumulation, the default or the small tile): no per-line tests are
+  // left in it.
   float se = 0.f, sd = 0.f;
-  auto tile = [&](auto full, auto inner) {
-    constexpr bool FULL = decltype(full)::value;
+  auto tile = [&](auto full_x, auto full_y, auto inner) {
+    constexpr int FX = decltype(full_x)::value, FY = decltype(full_y)::value;
+    constexpr bool FULL = FX > 0;
     // INNER: every source of the tile lies at least one pixel inside the image
     constexpr bool INNER = decltype(inner)::value;
-    // the full specialisation runs the default tile: its sizes are compile-time constants, so
-    // a footprint's second row and each line's accumulator are immediate offsets
-    const int TXk = FULL ? kSplatTileX : TX, TYk = FULL ? kSplatTileY : TY;
+    // the full specialisations' tile sizes are compile-time constants, so a footprint's second
+    // row and each line's accumulator are immediate offsets
+    const int TXk = FULL ? FX : TX, TYk = FULL ? FY : TY;
+    // their detector data, read before the source loop that hides the latency
+    constexpr int kPre = FULL ? FX * FY / kSplatThreads : 1;
+    float dpre[kPre];
+    if constexpr (FULL) {
+      static_assert(kPre * kSplatThreads == FX * FY, "whole pixels per thread");
+      if (mode == kSplatSplit) {
+#pragma unroll
+        for (int k = 0; k < kPre; ++k) {
+          const int i = tid + k * kSplatThreads;
+          const int y = min(ty0 + i / FX, ny - 1), x = min(tx0 + i % FX, nx - 1);
+          dpre[k] = ldg(G((const float*)p.d), (unsigned)(__mul24(y, nx) + x));
+        }
+      }
+    }
     const int PXk = TXk + 2, ptk = (TXk + 2) * (TYk + 2);
     const int pxm = __builtin_amdgcn_readfirstlane(PXk);  // row stride, a scalar operand
     const int plane = nx * ny;  // line stride of e (every offset below 2^31: L nx ny <= 16 * 4096^2)
@@ -523,13 +527,25 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
     }
   };
   const bool inner = sy0 >= 1 && sy1 <= ny - 2 && sx0 >= 1 && sx1 <= nx - 2;
+  using std::false_type;
+  using std::true_type;
+  constexpr std::integral_constant<int, 0> kAny{};
+  constexpr std::integral_constant<int, kSplatTileX> kTX{};
+  constexpr std::integral_constant<int, kSplatTileY> kTY{};
+  constexpr std::integral_constant<int, kSplatSmallX> kSX{};
+  constexpr std::integral_constant<int, kSplatSmallY> kSY{};
   if (fixed && L == NL && TX == kSplatTileX && TY == kSplatTileY) {
     if (inner)
-      tile(std::true_type{}, std::true_type{});
+      tile(kTX, kTY, true_type{});
     else
-      tile(std::true_type{}, std::false_type{});
+      tile(kTX, kTY, false_type{});
+  } else if (fixed && L == NL && TX == kSplatSmallX && TY == kSplatSmallY) {
+    if (inner)
+      tile(kSX, kSY, true_type{});
+    else
+      tile(kSX, kSY, false_type{});
   } else {
-    tile(std::false_type{}, std::false_type{});
+    tile(kAny, kAny, false_type{});
   }
   if (mode != kSplatForward && mode != kSplatLines && p.resid != nullptr) {
     __syncthreads();
@@ -634,14 +650,20 @@ void launch_splat_nl(const KArgs& a, int total_blocks, size_t lds, hipStream_t s
                        a.table);
 }
 
+// The line counts with an instance of their own (every other count runs the next larger one, with
+// a test per line): EPR_SPLAT_LINES(M) is M(1) M(2) ...
+#define EPR_SPLAT_LINES(M) M(1) M(2) M(3) M(4) M(5) M(8) M(10) M(16)
+
 // `lines` is the largest line count of the problems in the launch.
 hipError_t launch_splat(const KArgs& a, int total_blocks, size_t lds, hipStream_t s, int lines) {
-  if (lines <= 1) launch_splat_nl<1>(a, total_blocks, lds, s);
-  else if (lines <= 2) launch_splat_nl<2>(a, total_blocks, lds, s);
-  else if (lines <= 4) launch_splat_nl<4>(a, total_blocks, lds, s);
-  else if (lines <= 8) launch_splat_nl<8>(a, total_blocks, lds, s);
-  else launch_splat_nl<16>(a, total_blocks, lds, s);
-  return hipGetLastError();
+#define EPR_SPLAT_TRY(N)                           \
+  if (lines <= N) {                                \
+    launch_splat_nl<N>(a, total_blocks, lds, s);   \
+    return hipGetLastError();                      \
+  }
+  EPR_SPLAT_LINES(EPR_SPLAT_TRY)
+#undef EPR_SPLAT_TRY
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_resid_reduce(const KArgs& a, float* hist_slot, int nb, hipStream_t s) {
@@ -651,14 +673,13 @@ hipError_t launch_resid_reduce(const KArgs& a, float* hist_slot, int nb, hipStre
 
 hipError_t set_transport_attributes() {
   const int mx = 160 * 1024 - 1024;  // (room for the static LDS of the reductions)
-  const void* fns[] = {(const void*)k_splat<false, 1>, (const void*)k_splat<true, 1>,
-                       (const void*)k_splat<false, 2>, (const void*)k_splat<true, 2>,
-                       (const void*)k_splat<false, 4>, (const void*)k_splat<true, 4>,
-                       (const void*)k_splat<false, 8>, (const void*)k_splat<true, 8>,
-                       (const void*)k_splat<false, 16>, (const void*)k_splat<true, 16>,
-                       (const void*)k_splat_x<false, 1>, (const void*)k_splat_x<true, 1>, (const void*)k_splat_x<false, 2>, (const void*)k_splat_x<true, 2>,
-                       (const void*)k_splat_x<false, 4>, (const void*)k_splat_x<true, 4>, (const void*)k_splat_x<false, 8>, (const void*)k_splat_x<true, 8>,
-                       (const void*)k_splat_x<false, 16>, (const void*)k_splat_x<true, 16>};
+  const void* fns[] = {
+#define EPR_SPLAT_FNS(N)                                        \
+  (const void*)k_splat<false, N>, (const void*)k_splat<true, N>, \
+      (const void*)k_splat_x<false, N>, (const void*)k_splat_x<true, N>,
+      EPR_SPLAT_LINES(EPR_SPLAT_FNS)
+#undef EPR_SPLAT_FNS
+  };
   for (const void* f : fns) {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, mx);
     if (e != hipSuccess) return e;
