@@ -154,6 +154,14 @@ __device__ __forceinline__ float lane_right(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
 }
 
+// The same with the value `end` in the wave's first / last lane.
+__device__ __forceinline__ float lane_left_or(float v, float end) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(end), __float_as_int(v), 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float lane_right_or(float v, float end) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(end), __float_as_int(v), 0x130, 0xf, 0xf, false));
+}
+
 // Halo (in pixels, per axis) that covers every source whose bilinear footprint can reach a
 // tile: H = floor(max |u|) + 1, with max |u| = max_s |b_s| * max |D Y| (rounding is monotone,
 // so this bounds every per-source shift computed as b_s * D Y).  Capped at the image size.
