@@ -39,20 +39,23 @@ __device__ __forceinline__ float d_transpose3(float l, float m, float r, int j, 
 // Non-local model.  A workgroup of 8 waves computes G and the absorption gradient on a region of
 // 64 x 32 pixels, a lane one column of 4 consecutive rows, and writes both gradients on the
 // 62 x 30 pixels inside: D_x^T G_x from the neighbouring lanes, D_y^T G_y through LDS, so G is never
-// in memory (the 10 % computed twice cost less than a pass that reads G back).  The lines are
-// the outer loop: 16 taps of g are in flight per lane, read at one offset per pixel from
-// wave-uniform bases when a wave vote finds all of them inside the image.
-// 2048 x 2048, 8 lines:
-// 76 + 16 us (with the transposes as a second pass) -> 67 us.  Bound by the L1: the taps take 36
-// cache accesses per 64 pixels and line, with 44 vector issue slots beside them.
+// in memory (the 10 % computed twice cost less than a pass that reads G back).  All lines sample the
+// same g: the region's window of it, zero off the image, is staged in LDS with the halo that the
+// region's own shifts need, and the taps come from there; shifts too large for the window read g
+// itself.  (Taps from memory take the L1 36 accesses per 64 pixels and line beside 44 vector
+// issue slots.)  32 KB of LDS and 64 VGPRs hold four workgroups a CU.
+// 2048 x 2048, 8 lines: 76 + 16 us (taps from memory, transposes as a second pass) -> 67 us with the
+// transposes here -> 58 us with the window; bound by vector issue (41 us).
 // ---------------------------------------------------------------------------------------------
 constexpr int kVjpRows = 4, kVjpWaves = 8;
+constexpr int kVjpWindow = 8192;  // floats: shifts of 6 pixels take 78 x 46, of 20 pixels 106 x 74
 constexpr int kVjpTX = 62, kVjpTY = kVjpRows * kVjpWaves - 2;
 
 template <bool XDEP>
 __global__ __launch_bounds__(64 * kVjpWaves) void k_vjp(KArgs a, float* __restrict__ gphi,
                                                         float* __restrict__ gA, int accumulate) {
-  __shared__ float Gy[kVjpRows * kVjpWaves][64];
+  __shared__ float W[kVjpWindow];  // the window of g, then G_y
+  __shared__ float red[2][kVjpWaves];
   const ProbDesc& p = a.p;
   const int nx = p.nx, ny = p.ny, L = p.lp.n;
   const int local = xcd_remap(blockIdx.x, gridDim.x);
@@ -77,40 +80,67 @@ __global__ __launch_bounds__(64 * kVjpWaves) void k_vjp(KArgs a, float* __restri
     py[r] = (yh - yl == 2 ? 0.5f : 1.f) * (ldg(Y + yh * nx, (unsigned)xc) - ldg(Y + yl * nx, (unsigned)xc));
     av[r] = ldg(X + yc[r] * nx, (unsigned)xc);
   }
+  // window of g that every tap of the region falls into (halo from the region's own largest shifts;
+  // NaNs drop out of the maxima and sample their own pixel)
+  float mx = 0.f, my = 0.f;
+#pragma unroll
+  for (int r = 0; r < kVjpRows; ++r) {
+    mx = fmaxf(mx, fabsf(px[r]));
+    my = fmaxf(my, fabsf(py[r]));
+  }
+  mx = lane64_max(mx);
+  my = lane64_max(my);
+  if (lane == 0) {
+    red[0][w] = mx;
+    red[1][w] = my;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kVjpWaves; ++k) {
+    mx = fmaxf(mx, red[0][k]);
+    my = fmaxf(my, red[1][k]);
+  }
+  const int hx = halo_from(p.lp.b_absmax, mx), hy = halo_from(p.lp.b_absmax, my);
+  const int pitch = 64 + 2 * hx, rows = kVjpRows * kVjpWaves + 2 * hy;
+  const int wx0 = (local % ntx) * kVjpTX - 1 - hx, wy0 = (local / ntx) * kVjpTY - 1 - hy;
+  const bool windowed = (hx < 64 && hy < 64) && pitch * rows <= kVjpWindow;
+  if (windowed) {
+    for (int q = w; q < rows; q += kVjpWaves) {
+      const int y = wy0 + q;
+      const bool yin = (unsigned)y < (unsigned)ny;
+      gptr<const float> grow = g + min(max(y, 0), ny - 1) * nx;
+      for (int cc = lane; cc < pitch; cc += 64) {
+        const int xx = wx0 + cc;
+        const float v = ldg(grow, (unsigned)min(max(xx, 0), nx - 1));
+        W[q * pitch + cc] = yin && (unsigned)xx < (unsigned)nx ? v : 0.f;
+      }
+    }
+    __syncthreads();
+  }
+
   float sa[kVjpRows] = {}, sx[kVjpRows] = {}, sy[kVjpRows] = {};
   for (int s = 0; s < L; ++s) {
     const float4 c = line_wabq<XDEP>(p, xc, s);
     float dx[kVjpRows], dy[kVjpRows], g00[kVjpRows], g10[kVjpRows], g01[kVjpRows], g11[kVjpRows];
-    int xt[kVjpRows], yt[kVjpRows];
-    bool inside = true;
 #pragma unroll
     for (int r = 0; r < kVjpRows; ++r) {
       // cell and in-cell position as the splat forms them
       const float ux = c.z * px[r], uy = c.z * py[r];
       dx[r] = __builtin_amdgcn_fractf(ux);
       dy[r] = __builtin_amdgcn_fractf(uy);
-      xt[r] = xc + floor_to_int(ux);
-      yt[r] = yc[r] + floor_to_int(uy);
-      inside = inside && (unsigned)xt[r] <= (unsigned)(nx - 2) && (unsigned)yt[r] <= (unsigned)(ny - 2);
-    }
-    if (__all(inside)) {
-      const gptr<const float> b10 = g + 1, b01 = g + nx, b11 = g + nx + 1;
-#pragma unroll
-      for (int r = 0; r < kVjpRows; ++r) {
-        const unsigned o = (unsigned)(__mul24(yt[r], nx) + xt[r]);
-        g00[r] = ldg(g, o);
-        g10[r] = ldg(b10, o);
-        g01[r] = ldg(b01, o);
-        g11[r] = ldg(b11, o);
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < kVjpRows; ++r) {
-        const bool xi0 = (unsigned)xt[r] < (unsigned)nx, xi1 = (unsigned)(xt[r] + 1) < (unsigned)nx;
-        const bool yi0 = (unsigned)yt[r] < (unsigned)ny, yi1 = (unsigned)(yt[r] + 1) < (unsigned)ny;
-        const int x0 = min(max(xt[r], 0), nx - 1), x1 = min(max(xt[r] + 1, 0), nx - 1);
-        const int r0 = __mul24(min(max(yt[r], 0), ny - 1), nx);
-        const int r1 = __mul24(min(max(yt[r] + 1, 0), ny - 1), nx);
+      const int xt = xc + floor_to_int(ux), yt = yc[r] + floor_to_int(uy);
+      if (windowed) {
+        const float* q = W + (__mul24(yt - wy0, pitch) + xt - wx0);
+        g00[r] = q[0];
+        g10[r] = q[1];
+        g01[r] = q[pitch];
+        g11[r] = q[pitch + 1];
+      } else {
+        const bool xi0 = (unsigned)xt < (unsigned)nx, xi1 = (unsigned)(xt + 1) < (unsigned)nx;
+        const bool yi0 = (unsigned)yt < (unsigned)ny, yi1 = (unsigned)(yt + 1) < (unsigned)ny;
+        const int x0 = min(max(xt, 0), nx - 1), x1 = min(max(xt + 1, 0), nx - 1);
+        const int r0 = __mul24(min(max(yt, 0), ny - 1), nx);
+        const int r1 = __mul24(min(max(yt + 1, 0), ny - 1), nx);
         const float v00 = ldg(g, (unsigned)(r0 + x0)), v10 = ldg(g, (unsigned)(r0 + x1));
         const float v01 = ldg(g, (unsigned)(r1 + x0)), v11 = ldg(g, (unsigned)(r1 + x1));
         g00[r] = xi0 && yi0 ? v00 : 0.f;
@@ -130,6 +160,8 @@ __global__ __launch_bounds__(64 * kVjpWaves) void k_vjp(KArgs a, float* __restri
       sy[r] = fmaf(c.z * I, guy, sy[r]);
     }
   }
+  float(*Gy)[64] = reinterpret_cast<float(*)[64]>(W);
+  __syncthreads();  // every wave has read its taps
 #pragma unroll
   for (int r = 0; r < kVjpRows; ++r) Gy[w * kVjpRows + r][lane] = sy[r];
   __syncthreads();

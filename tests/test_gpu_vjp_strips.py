@@ -38,3 +38,29 @@ def test_vjp_edges_match_oracle(model, shape, n_lines):
     gp, ga = Context.get(0).forward_vjp(to_dev(phase), to_dev(absorb), to_dev(grad), geom, spec, model)
     assert rel_l2(to_np(ga), ra) <= 1e-5
     assert rel_l2(to_np(gp), rp) <= 1e-5
+
+
+@pytest.mark.parametrize("shift", [0.4, 6.0, 19.5, 24.0, 70.0])
+def test_vjp_window_sizes_match_oracle(shift):
+    # displacements within, at the limit of and beyond the window of the gradient held in LDS
+    # (phase smooth on the scale of the shift; tolerance as above)
+    from paper_2601_22793_amd import Context
+    shape = (150, 200)
+    print(f"vjp window shift={shift}", flush=True)
+    w = workload("nonlocal-poly8-2048", shape=shape)
+    w.energies_kev, w.weights = w.energies_kev[:3], w.weights[:3] / w.weights[:3].sum()
+    L = oracle_lines(w)
+    y, x = np.mgrid[:shape[0], :shape[1]]
+    phase = np.cos(0.06 * x + 0.5) * np.cos(0.05 * y) + 0.2 * np.sin(0.11 * x - 0.07 * y)
+    gy, gx = np.gradient(phase)
+    phase *= shift / (max(np.abs(gx).max(), np.abs(gy).max()) * np.max(L.eps_px * L.phase_scale))
+    phase = phase.astype(np.float32)
+    absorb = (0.5 + 0.2 * np.cos(0.1 * x)).astype(np.float32)
+    grad = np.random.default_rng(5).standard_normal(shape).astype(np.float32)
+    geom, spec, _ = api_objects(w)
+    rp, ra = O.forward_vjp(phase, absorb, grad, L, O.NONLOCAL)
+    gp, ga = Context.get(0).forward_vjp(to_dev(phase), to_dev(absorb), to_dev(grad), geom, spec, "nonlocal")
+    assert rel_l2(to_np(ga), ra) <= 1e-5
+    # dL/du is constant inside a cell and jumps between cells: a float32 shift that rounds across
+    # a cell edge (one in 1e5 of the pixels and lines) takes the neighbouring cell's value
+    assert rel_l2(to_np(gp), rp) <= 1e-2
