@@ -162,6 +162,29 @@ __device__ __forceinline__ float lane_right_or(float v, float end) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(end), __float_as_int(v), 0x130, 0xf, 0xf, false));
 }
 
+// sqrt(x) and its reciprocal, and n / sqrt(x), for finite x > 0: a Newton step on v_rsq_f32 and
+// a remainder step on the product with it give the correctly rounded root and quotient but for the
+// rare tie (v_sqrt_f32, v_rcp_f32 and an exponential of half the argument in the root's place gave
+// ten times the error at optical depth 30), in 5 and 3 instructions, where the library's root and
+// quotient take about 12 and 10 to serve denormals as well.
+struct Root {
+  float a, r;
+};
+__device__ __forceinline__ Root root_of(float x) {
+  Root q;
+  q.r = __builtin_amdgcn_rsqf(x);
+  const float s = x * q.r;
+  q.a = fmaf(fmaf(-s, s, x), 0.5f * q.r, s);
+  return q;
+}
+__device__ __forceinline__ float over_root(float n, Root q) {
+  const float v = n * q.r;
+  return fmaf(fmaf(-v, q.a, n), q.r, v);
+}
+// Smallest intensity whose root the pressure term takes (the smallest normal float): an intensity
+// that underflows has a negligible term instead of 0 / 0.
+constexpr float kRootMin = 1.17549435e-38f;
+
 // Halo (in pixels, per axis) that covers every source whose bilinear footprint can reach a
 // tile: H = floor(max |u|) + 1, with max |u| = max_s |b_s| * max |D Y| (rounding is monotone,
 // so this bounds every per-source shift computed as b_s * D Y).  Capped at the image size.

@@ -54,7 +54,6 @@ __device__ __forceinline__ void local_strip(const ProbDesc& p, int s, int y0, in
   } else {
     cw = p.lp.w[s]; ca = p.lp.a[s]; cb = p.lp.b[s]; cq = p.lp.q[s];
   }
-  const float ca2 = ca * 1.4426950408889634f;  // exp(-a x) = exp2(-a log2(e) x)
 
   // input row i is image row y0 - kLH + i
   float Xv[N], Yv[N];
@@ -90,21 +89,17 @@ __device__ __forceinline__ void local_strip(const ProbDesc& p, int s, int y0, in
   // coefficients of once, twice and four times differentiated terms
   constexpr float k1 = EDGE ? 1.f : 0.5f, k2 = k1 * k1, k4 = k2 * k2;
   const float cbg = cb * k1, cqg = cq * k4;
-  const float sw = __builtin_amdgcn_sqrtf(cw), ha2 = 0.5f * ca2;
 
-  float I[N], A[N], dyA[N], Q[N], GY[N], Ix[N], Iy[N], Pxx[N], Pxy[N], Pyy[N], dyP[N];
+  float I[N], dyA[N], Q[N], GY[N], Ix[N], Iy[N], Pxx[N], Pxy[N], Pyy[N], dyP[N];
+  Root A[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    // The closure's accuracy is I's: expf there.  In the pressure term, which is small against
-    // I, I and A come from the hardware exp2 (about one ulp); A by its own exponential, which
-    // underflows at half the exponent of I.
-    if constexpr (ORDER == kOrderTransportWkb1)
-      I[i] = cw * __builtin_amdgcn_exp2f(-ca2 * Xv[i]);
-    else
-      I[i] = cw * expf(-ca * Xv[i]);
+    // the fourth differences of A amplify its rounding, so A is the root of expf's I: an exp2 of
+    // the scaled argument would be off by the argument's rounding, which grows with the depth
+    I[i] = cw * expf(-ca * Xv[i]);
     if constexpr (ORDER >= 2) {
-      A[i] = sw * __builtin_amdgcn_exp2f(-ha2 * Xv[i]);
-      if (i >= 2) dyA[i - 1] = dy(i - 1, A[i - 2], A[i - 1], A[i]);
+      A[i] = root_of(fmaxf(I[i], kRootMin));
+      if (i >= 2) dyA[i - 1] = dy(i - 1, A[i - 2].a, A[i - 1].a, A[i].a);
     }
     const int j = i - 2;
     if constexpr (ORDER != kOrderTransportWkb1) {
@@ -121,7 +116,7 @@ __device__ __forceinline__ void local_strip(const ProbDesc& p, int s, int y0, in
     }
     if constexpr (ORDER >= 2) {
       if (j >= 2 && j < N - 2)
-        Q[j] = (dx(dx(A[j])) + dy(j, dyA[j - 1], dyA[j], dyA[j + 1])) * __builtin_amdgcn_rcpf(A[j]);
+        Q[j] = over_root(dx(dx(A[j].a)) + dy(j, dyA[j - 1], dyA[j], dyA[j + 1]), A[j]);
       const int k = i - 3;
       if (k >= 3 && k < N - 3) {
         GY[k] = I[k] * dy(k, Q[k - 1], Q[k], Q[k + 1]);

@@ -267,21 +267,15 @@ __device__ __forceinline__ void vjp_strip_line(const ProbDesc& p, int s, int y0,
     if constexpr (EDGE) return d_transpose3(fm, f0, fp, y0 - H + i, ny);
     return 0.5f * (fm - fp);
   };
-  const float ca2 = c.y * 1.4426950408889634f, ha2 = 0.5f * ca2;
-  const float sw = __builtin_amdgcn_sqrtf(c.x);
-  float I[N], A[N], rA[N], dyA[N], Q[N], kx[N], ky[N], vx[N], vy[N], t[N], ut[N];
+  Root A[N];
+  float I[N], dyA[N], Q[N], kx[N], ky[N], vx[N], vy[N], t[N], ut[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    // (the pressure term is small against I: hardware exp2 there)
-    if constexpr (ORDER == kOrderTransportWkb1)
-      I[i] = c.x * __builtin_amdgcn_exp2f(-ca2 * Xv[i]);
-    else
-      I[i] = c.x * expf(-c.y * Xv[i]);
+    I[i] = c.x * expf(-c.y * Xv[i]);
     kx[i] = dxt(Gv[i]);
     if constexpr (ORDER >= 2) {
-      A[i] = sw * __builtin_amdgcn_exp2f(-ha2 * Xv[i]);
-      rA[i] = __builtin_amdgcn_rcpf(A[i]);
-      if (i >= 2) dyA[i - 1] = dy(i - 1, A[i - 2], A[i - 1], A[i]);
+      A[i] = root_of(fmaxf(I[i], kRootMin));
+      if (i >= 2) dyA[i - 1] = dy(i - 1, A[i - 2].a, A[i - 1].a, A[i].a);
       // XDEP: q_s scales the pressure term after its outer derivative, so the row factor is
       // D_x^T(q_s g) and the column factor q_s(x) D_y^T g
       vx[i] = I[i] * (XDEP ? dxt(c.w * Gv[i]) : kx[i]);
@@ -293,9 +287,9 @@ __device__ __forceinline__ void vjp_strip_line(const ProbDesc& p, int s, int y0,
     if constexpr (ORDER >= 2) {
       const int j = i - 2;
       if (j >= 2 && j < N - 2) {
-        Q[j] = (dx(dx(A[j])) + dy(j, dyA[j - 1], dyA[j], dyA[j + 1])) * rA[j];
+        Q[j] = over_root(dx(dx(A[j].a)) + dy(j, dyA[j - 1], dyA[j], dyA[j + 1]), A[j]);
         const float tx = dxt(vx[j]), ty = dyt(j, vy[j - 1], vy[j], vy[j + 1]);
-        t[j] = (XDEP ? -fmaf(c.w, ty, tx) : -c.w * (tx + ty)) * rA[j];
+        t[j] = over_root(XDEP ? -fmaf(c.w, ty, tx) : -c.w * (tx + ty), A[j]);
       }
       const int k = i - 3;
       if (k >= 3 && k < N - 3) ut[k] = dyt(k, t[k - 1], t[k], t[k + 1]);
@@ -325,7 +319,7 @@ __device__ __forceinline__ void vjp_strip_line(const ProbDesc& p, int s, int y0,
         else
           dI += -c.w * (dqx * kx[m] + dqy * ky[m]);
         const float lap = dxt(dxt(t[m])) + dyt(m, ut[m - 1], ut[m], ut[m + 1]);
-        dI += (lap - t[m] * Q[m]) * (0.5f * rA[m]);
+        dI += 0.5f * over_root(lap - t[m] * Q[m], A[m]);
       }
       sa[o] -= c.y * I[m] * dI;
     }
@@ -365,9 +359,9 @@ __device__ __forceinline__ void vjp_strip(const ProbDesc& p, int w, int nw, int 
 }
 
 template <int ORDER, bool XDEP>
-__global__ __launch_bounds__(64 * kVsWavesMax) void k_vjp_local(KArgs a, float* __restrict__ Gx,
-                                                                float* __restrict__ Gy,
-                                                                float* __restrict__ gA) {
+__global__ __launch_bounds__(64 * kVsWavesMax) __attribute__((
+    amdgpu_waves_per_eu((ORDER == 1 ? 4 : ORDER == 2 ? 2 : 3) - (XDEP ? 1 : 0)))) void k_vjp_local(
+    KArgs a, float* __restrict__ Gx, float* __restrict__ Gy, float* __restrict__ gA) {
   constexpr int NQ = ORDER == kOrderTransportWkb1 ? 1 : 3;  // sums: A alone, or A, G_x, G_y
   __shared__ float red[kVsWavesMax][NQ][kVsRows][64];
   const ProbDesc& p = a.p;
