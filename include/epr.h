@@ -403,7 +403,9 @@ int epr_get_diagnostics(epr_handle h, epr_diagnostics* out);
  * reads, are representative.  The dimensions are tuned one after the other, each with the
  * others at their best so far; a candidate replaces the value in use only when it is at least
  * 1 % faster (smaller differences are timing noise).  The choices are kept on the handle for
- * every later call
+ * every later call, of single images (which without a tuned choice go by their size) and of
+ * batches; only an oversampled solve whose factor does not divide the tile's sides takes the
+ * default tile
  * (sizes are those of the internal grid when opts->oversample > 1).  The problems' data and
  * thickness are only read; the handle's cached batched graph is replaced (the next
  * epr_solve_batched captures its own again) and epr_get_diagnostics still reports on the

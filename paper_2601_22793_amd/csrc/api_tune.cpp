@@ -144,6 +144,8 @@ int epr_autotune(epr_handle h, int32_t n, const epr_problem* problems, const epr
         h->fft_row_var = rv;
         h->fft_col_var = cv;
         h->row_lines = lines;
+        h->tile_tuned = h->tile_tuned || kv.count("splat_tx");
+        h->lines_tuned = h->lines_tuned || kv.count("row_lines");
         ++h->tune_gen;
         return EPR_OK;
       }
@@ -206,11 +208,12 @@ int epr_autotune(epr_handle h, int32_t n, const epr_problem* problems, const epr
       rc = launch_iteration(h, p, opts->model, st, nullptr);
   }
 
-  // Every choice is timed on what the solvers run: one iteration of the batched solve of all
-  // the given problems (a batch of one for a single problem), replayed from its graph, on the
-  // warm copies.  The dimensions are tuned one after the other, each with the others at their
-  // best so far: splat tile, lines per row-pass workgroup, then the radix order of each row and
-  // column length.
+  // Every choice is timed on one iteration of the batched solve of all the given problems (a
+  // batch of one for a single problem), replayed from its graph, on the warm copies.  The solve of
+  // a single image takes the same choices; of small images only its row inverse differs from the
+  // batch's (several lines at once).  The dimensions are tuned one after the other, each with the
+  // others at their best so far: splat tile, lines per row-pass workgroup, then the radix order of
+  // each row and column length.
   std::vector<epr_problem> tp(problems, problems + n);
   for (int i = 0; i < n; ++i)
     tp[i].thickness = reinterpret_cast<float*>(static_cast<char*>(h->tune_tau.ptr) + tau_off[i]);
@@ -259,8 +262,10 @@ int epr_autotune(epr_handle h, int32_t n, const epr_problem* problems, const epr
       if (kSplatCand[c][0] == h->splat_tx && kSplatCand[c][1] == h->splat_ty) cur = c;
     tune(tiles, [&](int c) { h->splat_tx = kSplatCand[c][0]; h->splat_ty = kSplatCand[c][1]; },
          cur);
+    h->tile_tuned = h->tile_tuned || rc == EPR_OK;
   }
   if (Lmax > 1) tune({1, 2, 4}, [&](int v) { h->row_lines = v; }, h->row_lines);
+  h->lines_tuned = h->lines_tuned || (Lmax > 1 && rc == EPR_OK);
   for (int len : rows) {
     const int nv = fft_row_variants(len);
     std::vector<int> vs;

@@ -501,17 +501,7 @@ int fill_desc(epr_ctx* h, const epr_geometry& g, const LineParams& lp, char* bas
   p->ny = g.ny;
   p->nx = g.nx;
   p->nblk = (g.nx / 2 + 1 + kColBlock - 1) / kColBlock;
-  p->splat_tx = h->splat_tx;
-  p->splat_ty = h->splat_ty;
-  // An image of fewer default tiles than CUs takes the small tile: four times the workgroups, a
-  // quarter of the pixels and less than half of the sources (with halos of 7 pixels) each.
-  // 256 x 256, 10 lines, shifts up to 32 pixels: splat 26.7 -> 8.4 us (with the instance for 10
-  // lines); 90 x 96, 4 lines: 8.3 -> 6.4 us.  (A tile that was tuned stays.)
-  if (p->splat_tx == kSplatTileX && p->splat_ty == kSplatTileY &&
-      ((g.ny + kSplatTileY - 1) / kSplatTileY) * ((g.nx + kSplatTileX - 1) / kSplatTileX) < 256) {
-    p->splat_tx = kSplatSmallX;
-    p->splat_ty = kSplatSmallY;
-  }
+  choose_tile(*h, g.ny, g.nx, &p->splat_tx, &p->splat_ty);
   p->lrows = local_rows(blocks_local_rows(g.ny, g.nx, lp.n, 16), lp.n);
   p->lp = lp;
   p->os = 1;
@@ -535,21 +525,13 @@ int fill_desc(epr_ctx* h, const epr_geometry& g, const LineParams& lp, char* bas
 }
 
 // Internal grid of oversampling factor f.  The bin mode needs splat tiles of whole detector
-// pixels: a tuned tile that is not takes the default one's place.
+// pixels: the default tile takes the place of a tuned one whose sides are not multiples of f.
 void set_oversample(ProbDesc* p, int f) {
   p->os = f;
   if (p->splat_tx % f || p->splat_ty % f) {
     p->splat_tx = kSplatTileX;
     p->splat_ty = kSplatTileY;
   }
-}
-
-// The solves' row pass takes the tuned lines per workgroup, or fewer where that would leave a
-// single image less than four workgroups a CU (the lines of a workgroup run one after the other).
-// Row pass of 256 x 256, 10 lines: 12.9 -> 8.8 us; of 1215 x 1500, 4 lines: 37 -> 31 us.
-void apply_row_lines(const epr_ctx* h, ProbDesc* p, bool single_image) {
-  p->rlpb = h->row_lines;
-  while (single_image && p->rlpb > 1 && blocks_rowfft(*p) < 1024) p->rlpb /= 2;
 }
 
 KArgs single(const ProbDesc& p, int mode) {
