@@ -15,12 +15,11 @@ constexpr int kTuneReps = 3;
 constexpr float kTuneMargin = 0.01f;
 const int kSplatCand[][2] = {{64, 32}, {32, 32}, {64, 16}, {32, 64}, {128, 16}, {64, 64},
                              {128, 32}, {32, 16}};
-constexpr size_t kLdsLimit = 160 * 1024 - 64;
 
 // Is a splat tile usable for problems of L lines (LDS of the bordered per-line accumulators)?
 bool splat_tile_ok(int tx, int ty, int L) {
   if (tx < 8 || ty < 8 || tx > 256 || ty > 256 || tx * ty > 4096) return false;
-  return sizeof(float) * (size_t)L * (tx + 2) * (ty + 2) <= kLdsLimit;
+  return sizeof(float) * (size_t)L * (tx + 2) * (ty + 2) <= kSplatLdsMax;
 }
 
 // The tuning cache: one flat JSON object of integers, {"splat_tx": 64, "splat_ty": 32,

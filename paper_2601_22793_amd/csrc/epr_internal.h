@@ -37,6 +37,8 @@ __host__ __device__ inline int seg_band(int y, int ny) {
   return ny <= kMaxgBlocks ? y : ((y + 1) * kMaxgBlocks - 1) / ny;
 }
 constexpr int kSplatThreads = 512;
+constexpr int kSplatScratch = 16;  // floats of static LDS of the splat
+constexpr int kSplatLdsMax = 160 * 1024 - (int)sizeof(float) * kSplatScratch;  // most dynamic LDS
 constexpr int kSplatTileX = 64;  // default splat tile (columns x rows)
 constexpr int kSplatTileY = 32;
 constexpr int kSplatSmallX = 32; // tile of a single image with fewer default tiles than CUs

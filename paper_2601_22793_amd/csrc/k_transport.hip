@@ -211,7 +211,9 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
   // without per-corner bounds checks; the border is discarded.
   extern __shared__ unsigned int acc_u[];
   float* acc_f = reinterpret_cast<float*>(acc_u);
-  __shared__ float red[2][kSplatThreads / 64];
+  // the reductions of the prologue and of the residual, in turn: no more than that, so that every
+  // tile whose accumulators fit kSplatLdsMax launches
+  __shared__ __attribute__((aligned(16))) float scratch[kSplatScratch];
   const int nx = p.nx, ny = p.ny;
   const int TX = p.splat_tx, TY = p.splat_ty;
   const int ptile = (TX + 2) * (TY + 2);
@@ -230,40 +232,50 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
   }
 
   // Halo of the tile and minimum of X.  The segment maxima around the tile (kGuessX columns and
-  // kGuessY rows away, one entry per thread) bound the shifts of the sources there, by sign; the
+  // kGuessY rows away) bound the shifts of the sources there, by sign; the
   // partials' maximum bounds every shift of the image.  When the latter keeps all sources that
   // reach the tile within the former's surroundings, the former gives the tile's halo: a tile
-  // away from the steepest edges reads few sources that it does not need.  All in the first
-  // kScanWaves waves, with one barrier.
+  // away from the steepest edges reads few sources that it does not need.  The first three waves
+  // read the segments and the fourth the partials, with one barrier.
   // 2048 x 2048, 8 lines, shifts up to 6 pixels: splat 84 -> 66 us a launch (73 us of it by the
   // halo and this prologue, the rest by reading the detector data before the source loop);
   // max-gradient 7.5 -> 8.3 us for the signed segment maxima.
   constexpr int kGuessX = kSegCols, kGuessY = kSplatTileY / 2;
-  constexpr int kScanWaves = kMaxgBlocks / 64;
-  static_assert(kScanWaves * 64 <= kSplatThreads, "one partial per thread");
-  __shared__ float4 red4[kScanWaves][2];
+  constexpr int kScanWaves = 3, kScanMax = 256;
+  static_assert(kMaxgBlocks == 4 * 64, "four partials (three float4) a lane");
+  static_assert(4 * kScanWaves + 3 <= kSplatScratch && 4 * 4 <= kSplatScratch &&
+                2 * (kSplatThreads / 64) <= kSplatScratch, "scratch");
+  float4* const red4 = reinterpret_cast<float4*>(scratch);
   const int nseg = seg_cols(nx);
   gptr<const float4> segs = G((const float4*)p.segs);
   const int gs0 = max(tx0 - kGuessX, 0) / kSegCols;
   const int gns = min(tx0 + TX - 1 + kGuessX, nx - 1) / kSegCols - gs0 + 1;
   const int gb0 = seg_band(max(ty0 - kGuessY, 0), ny);
   const int gn = gns * (seg_band(min(ty0 + TY - 1 + kGuessY, ny - 1), ny) - gb0 + 1);
-  if (tid < kMaxgBlocks) {
-    gptr<const float> mg = G(p.maxg);
+  if (tid < kScanWaves * 64) {
     float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (tid < gn) m = ldg(segs, (unsigned)((gb0 + tid / gns) * nseg + gs0 + tid % gns));
-    float gx = ldg(mg, (unsigned)(3 * tid)), gy = ldg(mg, (unsigned)(3 * tid + 1));
-    float xmin = ldg(mg, (unsigned)(3 * tid + 2));
-    m.x = lane64_max(m.x);
-    m.y = lane64_max(m.y);
-    m.z = lane64_max(m.z);
-    m.w = lane64_max(m.w);
-    gx = lane64_max(gx);
-    gy = lane64_max(gy);
-    xmin = -lane64_max(-xmin);
+#pragma unroll
+    for (int k = 0; k * kScanWaves * 64 < kScanMax; ++k) {
+      const int i = tid + k * kScanWaves * 64;
+      if (i < min(gn, kScanMax)) {
+        const float4 v = ldg(segs, (unsigned)((gb0 + i / gns) * nseg + gs0 + i % gns));
+        m = make_float4(fmaxf(m.x, v.x), fmaxf(m.y, v.y), fmaxf(m.z, v.z), fmaxf(m.w, v.w));
+      }
+    }
+    m = make_float4(lane64_max(m.x), lane64_max(m.y), lane64_max(m.z), lane64_max(m.w));
+    if ((tid & 63) == 0) red4[tid >> 6] = m;
+  } else if (tid < (kScanWaves + 1) * 64) {
+    // partials {x, y, min} of four bands: a.x a.y a.z, a.w b.x b.y, b.z b.w c.x, c.y c.z c.w
+    gptr<const float4> mg = (gptr<const float4>)G(p.maxg);
+    const unsigned i = 3u * (unsigned)(tid & 63);
+    const float4 a = ldg(mg, i), b = ldg(mg, i + 1), c = ldg(mg, i + 2);
+    const float gx = lane64_max(fmaxf(fmaxf(a.x, a.w), fmaxf(b.z, c.y)));
+    const float gy = lane64_max(fmaxf(fmaxf(a.y, b.x), fmaxf(b.w, c.z)));
+    const float xm = -lane64_max(-fminf(fminf(a.z, b.y), fminf(c.x, c.w)));
     if ((tid & 63) == 0) {
-      red4[tid >> 6][0] = m;
-      red4[tid >> 6][1] = make_float4(gx, gy, xmin, 0.f);
+      scratch[4 * kScanWaves] = gx;
+      scratch[4 * kScanWaves + 1] = gy;
+      scratch[4 * kScanWaves + 2] = xm;
     }
   }
   {
@@ -274,36 +286,37 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
     if (tid < (n & 3)) acc_u[(n & ~3) + tid] = 0u;
   }
   __syncthreads();
-  float4 sm = red4[0][0], gm = red4[0][1];
+  float4 sm = red4[0];
 #pragma unroll
   for (int w = 1; w < kScanWaves; ++w) {
-    const float4 a = red4[w][0], b = red4[w][1];
+    const float4 a = red4[w];
     sm = make_float4(fmaxf(sm.x, a.x), fmaxf(sm.y, a.y), fmaxf(sm.z, a.z), fmaxf(sm.w, a.w));
-    gm.x = fmaxf(gm.x, b.x);
-    gm.y = fmaxf(gm.y, b.y);
-    gm.z = fminf(gm.z, b.z);
   }
-  const float xmin = gm.z;
-  const int hx = halo_from(p.lp.b_absmax, gm.x);
-  const int hy = halo_from(p.lp.b_absmax, gm.y);
-  if (hx > kGuessX || hy > kGuessY || gn > kMaxgBlocks) {
+  const float gmx = scratch[4 * kScanWaves], gmy = scratch[4 * kScanWaves + 1];
+  const float xmin = scratch[4 * kScanWaves + 2];
+  const int hx = halo_from(p.lp.b_absmax, gmx);
+  const int hy = halo_from(p.lp.b_absmax, gmy);
+  if (hx > kGuessX || hy > kGuessY || gn > kScanMax) {
     // sources from further away (or too many entries above): the segments the image's halo spans
     const int s0 = max(tx0 - hx, 0) / kSegCols, s1 = min(tx0 + TX - 1 + hx, nx - 1) / kSegCols;
     const int b0 = seg_band(max(ty0 - hy, 0), ny), b1 = seg_band(min(ty0 + TY - 1 + hy, ny - 1), ny);
     const int ns = s1 - s0 + 1;
-    float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int i = tid; i < ns * (b1 - b0 + 1); i += kSplatThreads) {
-      const float4 v = ldg(segs, (unsigned)((b0 + i / ns) * nseg + s0 + i % ns));
-      m = make_float4(fmaxf(m.x, v.x), fmaxf(m.y, v.y), fmaxf(m.z, v.z), fmaxf(m.w, v.w));
+    constexpr int kFarWaves = 4;
+    __syncthreads();  // every wave has read the scratch
+    if (tid < kFarWaves * 64) {
+      float4 m = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int i = tid; i < ns * (b1 - b0 + 1); i += kFarWaves * 64) {
+        const float4 v = ldg(segs, (unsigned)((b0 + i / ns) * nseg + s0 + i % ns));
+        m = make_float4(fmaxf(m.x, v.x), fmaxf(m.y, v.y), fmaxf(m.z, v.z), fmaxf(m.w, v.w));
+      }
+      m = make_float4(lane64_max(m.x), lane64_max(m.y), lane64_max(m.z), lane64_max(m.w));
+      if ((tid & 63) == 0) red4[tid >> 6] = m;
     }
-    __shared__ float4 redw[kSplatThreads / 64];
-    m = make_float4(lane64_max(m.x), lane64_max(m.y), lane64_max(m.z), lane64_max(m.w));
-    if ((tid & 63) == 0) redw[tid >> 6] = m;
     __syncthreads();
-    sm = redw[0];
+    sm = red4[0];
 #pragma unroll
-    for (int w = 1; w < kSplatThreads / 64; ++w) {
-      const float4 a = redw[w];
+    for (int w = 1; w < kFarWaves; ++w) {
+      const float4 a = red4[w];
       sm = make_float4(fmaxf(sm.x, a.x), fmaxf(sm.y, a.y), fmaxf(sm.z, a.z), fmaxf(sm.w, a.w));
     }
   }
@@ -552,15 +565,15 @@ __device__ __forceinline__ void splat_body(const ProbDesc& p, int local, int mod
     se = wave_sum(se);
     sd = wave_sum(sd);
     if ((tid & 63) == 0) {
-      red[0][tid >> 6] = se;
-      red[1][tid >> 6] = sd;
+      scratch[2 * (tid >> 6)] = se;
+      scratch[2 * (tid >> 6) + 1] = sd;
     }
     __syncthreads();
     if (tid == 0) {
       float te = 0.f, td = 0.f;
       for (int w = 0; w < kSplatThreads / 64; ++w) {
-        te += red[0][w];
-        td += red[1][w];
+        te += scratch[2 * w];
+        td += scratch[2 * w + 1];
       }
       G(p.resid)[2 * local] = te;
       G(p.resid)[2 * local + 1] = td;
@@ -672,7 +685,6 @@ hipError_t launch_resid_reduce(const KArgs& a, float* hist_slot, int nb, hipStre
 }
 
 hipError_t set_transport_attributes() {
-  const int mx = 160 * 1024 - 1024;  // (room for the static LDS of the reductions)
   const void* fns[] = {
 #define EPR_SPLAT_FNS(N)                                        \
   (const void*)k_splat<false, N>, (const void*)k_splat<true, N>, \
@@ -681,7 +693,7 @@ hipError_t set_transport_attributes() {
 #undef EPR_SPLAT_FNS
   };
   for (const void* f : fns) {
-    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, mx);
+    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSplatLdsMax);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

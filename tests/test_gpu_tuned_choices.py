@@ -41,6 +41,36 @@ def test_cached_tile_is_the_one_a_small_image_runs(tmp_path, shape):
             c.close()
 
 
+@pytest.mark.parametrize("tile,n_lines", [((60, 64), 10), ((32, 84), 14), ((10, 211), 16)])
+def test_largest_accepted_tiles_match_oracle(tmp_path, tile, n_lines):
+    # tiles whose accumulators leave 64 to 320 bytes of a CU's 160 KB (tolerance of the solves)
+    import torch
+    from paper_2601_22793_amd import Context
+    shape = (120, 250)
+    w = workload("nonlocal-poly8-2048", shape=shape, n_iter=3)
+    w.energies_kev = 60.0 + 100.0 * (np.arange(n_lines) + 0.5) / n_lines
+    w.weights = np.full(n_lines, 1.0 / n_lines)
+    obj = w.true_object()
+    L = oracle_lines(w)
+    d = w.add_noise(O.forward(obj["phase"], obj["absorb"], L, O.NONLOCAL))
+    ref = O.solve(d, L, O.NONLOCAL, 3, 0.4)
+    geom, spec, mat = api_objects(w)
+    entry = (to_dev(d), torch.zeros(shape, dtype=torch.float32, device="cuda"), geom, spec, mat)
+    c = Context(0)
+    try:
+        path = str(tmp_path / "tile.json")
+        with open(path, "w") as fh:
+            json.dump({"splat_tx": tile[0], "splat_ty": tile[1]}, fh)
+        got = c.autotune([entry], "nonlocal", cache_json=path)
+        assert (got["splat_tx"], got["splat_ty"]) == tile
+        print(f"tile {tile} x {n_lines} lines", flush=True)
+        assert rel_l2(to_np(c.solve(entry[0], geom, spec, mat, "nonlocal", 3, 0.4)), ref) <= 1e-4
+        c.solve_batched([entry], "nonlocal", 3, 0.4)
+        assert rel_l2(to_np(entry[1]), ref) <= 1e-4
+    finally:
+        c.close()
+
+
 @pytest.mark.parametrize("lines", [0, 1, 2, 4])
 @pytest.mark.parametrize("shape,n_lines", [((96, 128), 8), ((64, 250), 3), ((2048, 64), 8),
                                            ((60, 2560), 5)])
