@@ -36,6 +36,8 @@ __device__ __forceinline__ void fetch_row_tiles(gptr<const float2> sp, float2* d
   }
 }
 
+constexpr float kThick = 8.f;  // largest a_s tau of the update's difference form
+
 // GR: lines transformed at once, by groups of NT threads (GR NT threads a workgroup).
 // XDEP: x-dependent spectrum, the update and projection constants are read per column.
 // BLK (with XDEP): block-wise preconditioner.  Each line has p.nbp filtered spectra, one per
@@ -80,14 +82,17 @@ __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
       if (live[k % kPerRow]) tv[k] = ldg(G((const float*)p.tau), (unsigned)(__mul24(y, nx) + x));
     acc[k] = 0.f;
   }
-  // some a_s tau of the wave's pixels leaves the range of the update's difference form
-  bool thick = false;
+  // A pixel is thick if some a_s tau of it leaves the range of the update's difference form (a NaN
+  // does not: that form carries it on).  any_thick: the wave has such a pixel.
+  float amax = 0.f;
+  bool any_thick = false;
   if constexpr (SOLVE) {
-    float amax = 0.f, tmax = 0.f;
+    float tmax = 0.f;
     for (int s = 0; s < L; ++s) amax = fmaxf(amax, p.lp.a_hi[s]);
+    amax = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(amax)));
 #pragma unroll
     for (int k = 0; k < SC::kPix; ++k) tmax = fmaxf(tmax, tv[k]);
-    thick = __any(!(amax * tmax <= 8.f));
+    any_thick = __any(amax * tmax > kThick);
   }
   const float odd_sign = (tid & 1) ? -1.f : 1.f;  // NT is even: x has the parity of tid
   const RowPix<NT> pix(tid);
@@ -169,12 +174,18 @@ __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
       // logarithm of it, rounded, would give tau back to a few 1e-7 only in every iteration
       // (errors of whole solves: halved for multi-pixel shifts, a fifth for the local closure).
       // exp and ln through the hardware base-2 transcendentals (v_exp_f32 / v_log_f32, about one
-      // ulp).  Waves that hold a pixel with a_s tau > 8 (transmission below 3e-4, where a new
-      // thickness far from tau would cancel) take -ln(max(exp(-a_s tau) + z, 1e-6)) as it stands.
+      // ulp).  Pixels with a_s tau > 8 (transmission below 3e-4, where a new thickness far from tau
+      // would cancel) take -ln(max(exp(-a_s tau) + z, 1e-6)) as it stands: each pixel by its own
+      // thickness, so its rounding does not depend on the pixels that share its wave; only waves
+      // that hold such a pixel form both.
       const float la2 = p.lp.a[s] * 1.4426950408889634f;
       const float mws_ln2 = p.lp.mw[s] * 0.69314718055994531f;
       const float om = p.relax, om_w = p.relax * p.lp.inv_w[s];
-      auto update = [&](auto difference) {
+      auto update = [&](auto mixed) {
+        // (opaque to the optimiser, which would keep the comparisons of the mixed form as 16 lane
+        // masks through the loop over the lines and spill scalar registers)
+        float am = amax;
+        if constexpr (decltype(mixed)::value) asm volatile("" : "+s"(am));
 #pragma unroll
         for (int j = 0; j < kPerRow; ++j) {
           const int x = tid + j * NT;
@@ -199,25 +210,24 @@ __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
             }
             chk += v;
             const float t2 = c_a2 * tv[k], z = c_z * v;
-            float l;
-            if constexpr (decltype(difference)::value) {
-              const float E = __builtin_amdgcn_exp2f(t2);
-              const float u = fmaf(z, E, 1.f);
-              // what the rounding of 1 + z E dropped, as far as it matters: the logarithm needs
-              // du / u, which is du for u near 1 and, bounded so, below its rounding elsewhere
-              const float du = __builtin_amdgcn_fmed3f(fmaf(z, E, 1.f - u), -1.2e-7f, 1.2e-7f);
-              l = fmaf(du, 1.4426950408889634f, __builtin_amdgcn_logf(fmaxf(u, 1e-6f * E)));
-            } else {
-              l = __builtin_amdgcn_logf(fmaxf(z + __builtin_amdgcn_exp2f(-t2), 1e-6f));
+            const float E = __builtin_amdgcn_exp2f(t2);
+            const float u = fmaf(z, E, 1.f);
+            // what the rounding of 1 + z E dropped, as far as it matters: the logarithm needs
+            // du / u, which is du for u near 1 and, bounded so, below its rounding elsewhere
+            const float du = __builtin_amdgcn_fmed3f(fmaf(z, E, 1.f - u), -1.2e-7f, 1.2e-7f);
+            float l = fmaf(du, 1.4426950408889634f, __builtin_amdgcn_logf(fmaxf(u, 1e-6f * E)));
+            if constexpr (decltype(mixed)::value) {
+              const float r = fmaxf(z + __builtin_amdgcn_exp2f(-t2), 1e-6f);
+              l = am * tv[k] > kThick ? __builtin_amdgcn_logf(r) : l;
             }
             acc[k] = fmaf(c_mw, l, acc[k]);
           }
         }
       };
-      if (thick)
-        update(std::false_type{});
-      else
+      if (__builtin_expect(any_thick, 0))
         update(std::true_type{});
+      else
+        update(std::false_type{});
     } else {
       gptr<float> o = G(p.out) + (size_t)s * nx * ny;
 #pragma unroll
@@ -257,7 +267,7 @@ __device__ __forceinline__ void rowinv_body(const ProbDesc& p, int local, int) {
         }
         float id = inv_den;
         if constexpr (XDEP) id = ldg(G(p.xden), (unsigned)x);
-        const float t = fmaf(-sum, id, thick ? 0.f : tv[k]);
+        const float t = fmaf(-sum, id, amax * tv[k] > kThick ? 0.f : tv[k]);
         bad = bad || !(fabsf(t) <= 3.40282347e38f);
         stg(G(p.tau), (unsigned)(__mul24(y, nx) + x), t);
         if (p.phase_out) stg(G(p.phase_out), (unsigned)(__mul24(y, nx) + x), pc * t);
