@@ -44,7 +44,7 @@ METRIC = "2048² projections/s to 1e-4 rel. phase err, batched vs plain; % HBM p
 UNIT = "2048^2 projections/s"
 HBM_PEAK_GBS = 8000.0
 STAGES = ("maxgrad", "splat", "local", "rowfft", "colfft", "rowinv", "vjp", "binsplit")
-KERNEL_SOURCE = {"maxgrad": "k_transport.hip", "splat": "k_transport.hip",
+KERNEL_SOURCE = {"maxgrad": "k_transport.hip", "splat": "k_splat.h",
                  "local": "k_local.hip", "rowfft": "k_rowfft.hip",
                  "colfft": "k_colfft.hip", "rowinv": "k_rowinv.hip", "vjp": "k_vjp.hip",
                  "binsplit": "k_transport.hip"}
@@ -123,8 +123,7 @@ def kernel_instance(stage, cls, batched, n_lines, row_lines):
     if stage in ("rowfft", "colfft", "rowinv"):
         return f"k_{stage}<{b}, {512 if cls == 0 else 1024}>"
     if stage == "splat":
-        nl = next(v for v in (1, 2, 3, 4, 5, 8, 10, 16) if v >= n_lines)
-        return f"k_splat<{b}, {nl}>"
+        return f"k_splat<{b}, {n_lines}>"
     return f"k_{stage}<{b}>"
 
 

@@ -25,6 +25,7 @@ LIB = os.path.join(PKG, "libepr.so")
 EXPORTS = "-Wl,--version-script=" + os.path.join(CSRC, "libepr.map")
 
 SOURCES = ["host_core.cpp", "api_ops.cpp", "api_solve.cpp", "api_batch.cpp", "api_tune.cpp", "k_transport.hip",
+           "k_splat_a.hip", "k_splat_b.hip", "k_splat_c.hip", "k_splat_d.hip", "k_splat_e.hip",
            "k_rowfft.hip", "k_colfft.hip", "k_rowinv.hip", "k_local.hip", "k_vjp.hip", "k_regime.hip", "noalloc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
