@@ -30,6 +30,7 @@ import hashlib
 import json
 import os
 import platform
+import re
 import sys
 import tempfile
 import time
@@ -114,25 +115,59 @@ def size_class(ny, nx):
     return 0 if (ny <= 2048 and nx <= 2048) else 1
 
 
-def kernel_instance(stage, cls, batched, n_lines, row_lines):
+def kernel_instance(stage, cls, batched, n_lines, row_lines, shapes, model):
     """Name of the kernel template instance a (stage, size class) launch runs, as rocprofv3
-    lists it (without the namespace).  row_lines: lines per row-pass workgroup."""
+    lists it (without the namespace).  row_lines: lines per row-pass workgroup; shapes: the
+    (rows, columns) of the launch's internal grids."""
     b = "true" if batched else "false"
+    nt = 512 if cls == 0 else 1024
     if stage == "rowfft":
-        return f"k_rowfft<{b}, {512 if cls == 0 else 1024}, {row_lines}>"
-    if stage in ("rowfft", "colfft", "rowinv"):
-        return f"k_{stage}<{b}, {512 if cls == 0 else 1024}>"
+        return f"k_rowfft<{b}, {nt}, {row_lines}>"
+    if stage == "colfft" and cls == 1 and max(ny for ny, _ in shapes) <= 2304:
+        return f"k_colfft_mid<{b}>"
+    if stage == "rowinv" and not batched and n_lines > 1 and shapes[0][1] <= 1024 and \
+            -(-shapes[0][0] // 4) <= 256:
+        nt, groups = (128, 8) if shapes[0][1] <= 512 and n_lines > 4 else \
+            (256, 4) if n_lines > 2 else (256, 2)
+        return f"k_rowinv_g<{nt}, {groups}, true, false>"
+    if stage in ("colfft", "rowinv"):
+        return f"k_{stage}<{b}, {nt}>"
     if stage == "splat":
         return f"k_splat<{b}, {n_lines}>"
+    if stage == "local":
+        strips = 1 if n_lines >= 3 else 2 if n_lines == 2 else 4
+        waves = sum(-(-ny // 16) * -(-nx // (56 * strips)) for ny, nx in shapes) * n_lines * strips
+        rows = 4 if waves < 256 else 8 if waves < 1024 or n_lines >= 16 else 16
+        order = {"local_l1": 1, "local_l2": 2}.get(model, 3)
+        return f"k_local<{b}, {rows}, {order}, false>"
     return f"k_{stage}<{b}>"
 
 
-def source_digest(stage):
-    """SHA-256 of the kernel's translation unit and the device headers it includes."""
+def row_pass_lines(batched, ny, n_lines, tuned):
+    """Lines per row-pass workgroup: the tuned number, else two, which a single image halves where
+    it would leave fewer than four workgroups a CU."""
+    if tuned and "row_lines" in tuned and n_lines > 1:
+        return tuned["row_lines"]
+    return 1 if not batched and -(-ny // 4) * -(-n_lines // 2) < 1024 else 2
+
+
+def source_files(stage):
+    """The kernel's source and every header of the library that it includes, directly or not."""
     csrc = os.path.join(ROOT, "paper_2601_22793_amd", "csrc")
+    files = [KERNEL_SOURCE[stage]]
+    for f in files:
+        for line in open(os.path.join(csrc, f)):
+            m = re.match(r'#include "(\w+\.h)"', line)
+            if m and m.group(1) not in files:
+                files.append(m.group(1))
+    return [os.path.join(csrc, f) for f in sorted(files)]
+
+
+def source_digest(stage):
+    """SHA-256 of the kernel's source and the device headers it includes."""
     h = hashlib.sha256()
-    for f in (KERNEL_SOURCE[stage], "dev_common.h", "epr_internal.h", "fft_lds.h", "spectral.h"):
-        h.update(open(os.path.join(csrc, f), "rb").read())
+    for f in source_files(stage):
+        h.update(open(f, "rb").read())
     return h.hexdigest()
 
 
@@ -423,8 +458,9 @@ def main():
         per_launch_bytes = stage_bytes(dom, members[0][2].ny, members[0][2].nx, L, f)
     avg_s = ms_total / 1e3 / max(launches, 1)
     achieved = per_launch_bytes / avg_s / 1e9
-    # (the library's default is two lines per row-pass workgroup when nothing was tuned)
-    kname = kernel_instance(dom, cls, batched, L, (tuned or {}).get("row_lines", 2))
+    shapes = [(p[2].ny * f, p[2].nx * f) for p in members]
+    kname = kernel_instance(dom, cls, batched, L, row_pass_lines(batched, shapes[0][0], L, tuned),
+                            shapes, model)
     ctr = counters_for(kname, dom, args.workload if f == 1 else f"{args.workload}-os{f}")
     valu = ctr.get("valu_insts_per_launch")
     roof = {"bound": "hbm", "kernel": kname, "achieved": round(achieved, 1),
