@@ -337,8 +337,8 @@ int epr_adjoint_xspec(epr_handle h, const epr_geometry* geom, const epr_spectrum
  * closures (Eq. 1, Methods 4.1) and the diffraction-pressure term of EPR_NONLOCAL_L2: the chain
  * rule through the derivative compositions of Eq. 1 with the exact transpose of D.  The ray maps
  * and closure terms are recomputed from `phase` and `absorb`; nothing is saved from the forward
- * call.  Uses the handle's workspace (2 + 2 n_lines planes of ny x nx floats for the
- * second-order models).  The gradients must not alias each other or the inputs. */
+ * call.  Uses the handle's workspace (two planes of ny x nx floats, for every
+ * model).  The gradients must not alias each other or the inputs. */
 int epr_forward_vjp(epr_handle h, const epr_geometry* geom, const epr_spectrum* spec, int model,
                     const float* phase, const float* absorb, const float* grad_intensity,
                     float* grad_phase, float* grad_absorb, void* stream);
@@ -422,8 +422,8 @@ int epr_autotune(epr_handle h, int32_t n, const epr_problem* problems, const epr
 /* Per-stage kernel timing with HIP events recorded on the launch stream around every stage
  * launch.
  * Stages: 0 max-gradient, 1 splat, 2 local closure, 3 row FFT (+ back-transport), 4 column
- * FFT + filter, 5 row inverse FFT + update, 6 vector-Jacobian product, 7 detector binning and
- * residual split (oversampled solves). */
+ * FFT + filter, 5 row inverse FFT + update, 6 vector-Jacobian product, 7 has no launches (the
+ * detector binning and residual split of oversampled solves are part of stages 1 and 2). */
 #define EPR_N_STAGES 8
 typedef struct {
   double ms[EPR_N_STAGES];        /* summed kernel time per stage since the last reset       */
@@ -445,8 +445,9 @@ int epr_get_timing(epr_handle h, epr_timing* out);
 
 /* Host-only helpers (no device needed). */
 
-/* Radix sequence of the library's FFT for length n (a product of 2, 3 and 5): writes up to
- * `capacity` radices to `radices` (host) and returns the number of stages, EPR_ERR_SHAPE if n
+/* Elementary radix sequence of an FFT of length n (a product of 2, 3 and 5: radix 16, then 8, 4
+ * or 2, then 5s and 3s; the library transforms the lengths that have one, in these or in fewer
+ * stages of composite radices, e.g. 1215 as 15 9 9): writes up to `capacity` radices to `radices` (host) and returns the number of stages, EPR_ERR_SHAPE if n
  * has another prime factor, EPR_ERR_INVALID_ARG for n < 1 or a NULL array with capacity > 0. */
 int epr_fft_plan(int32_t n, int32_t* radices, int32_t capacity);
 

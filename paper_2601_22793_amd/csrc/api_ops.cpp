@@ -306,7 +306,7 @@ int epr_forward_oversampled(epr_handle h, const epr_geometry* geom, const epr_sp
   p.X = absorb;
   p.Y = phase;
   set_oversample(&p, oversample);
-  p.d = nullptr;         // the bin-split pass writes the binned prediction to out
+  p.d = nullptr;         // the bin mode writes the binned prediction to out
   p.out = intensity;
   p.resid = nullptr;
   const int cls = spectral_threads(p) == 1024 ? 1 : 0;

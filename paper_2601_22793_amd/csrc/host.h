@@ -225,7 +225,7 @@ struct DeviceGuard {
   } while (0)
 
 enum Stage { kStMaxg = 0, kStSplat = 1, kStLocal = 2, kStRowFft = 3, kStColFft = 4,
-             kStRowInv = 5, kStVjp = 6 };  // (stage 7, the bin-split pass, is part of 1 and 2)
+             kStRowInv = 5, kStVjp = 6 };  // (7, the detector binning, has no launches: it is part of 1 and 2)
 
 // Launches of a batched iteration.
 enum BatchStage { kBsMaxg, kBsSplatSplit, kBsSplatLines, kBsSplatBin, kBsLocalSplit, kBsLocalBin,

@@ -18,9 +18,11 @@
 // at the end (one barrier).  A workgroup holds one wave per line and strip: local_strips(L)
 // strips of every line, so that few-line problems still fill a workgroup.
 //
-// Bound by vector issue (about 75 instructions per row, line and wave).  Against a version that
+// Bound by vector issue (about 80 instructions per row, line and wave).  Against a version that
 // walked the levels of derivatives over 24 x 24 LDS regions with five barriers per line:
-// 1080 x 1200, 4 lines: 159 -> 29 us a launch; 256 x 256, 1 line: 8.4 -> 6.9 us.
+// 1080 x 1200, 4 lines: 159 -> 33 us a launch; 256 x 256, 1 line: 8.4 -> 7.0 us.  (An A from its own
+// hardware exponential and v_rcp_f32 in the quotients ran in 32 and 6.5 us, with ten times the
+// error in the pressure term at optical depth 30.)
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

@@ -223,7 +223,8 @@ __global__ __launch_bounds__(kTrThreads) void k_vjp_transpose(KArgs a, const flo
 // derivatives (four deep in t) needs no planes in memory.  The waves of a workgroup share the lines
 // of one strip and add their sums through LDS at the end.
 // Bound by vector issue.  1024 x 1280, 4 lines, pressure term: 138 us (four passes over per-line
-// planes of A, Q and t) -> 24 us.
+// planes of A, Q and t) -> 28 us.  The registers are held to what three waves per SIMD allow
+// (two with ORDER 2), or one wave fewer with a spectrum per column, where that would spill.
 // ---------------------------------------------------------------------------------------------
 constexpr int kVsRows = 8;
 constexpr int kVsWavesMax = 4;

@@ -10,7 +10,8 @@
 //
 // Every kernel is instantiated for two size classes, NT = 512 threads (nx, ny <= 2048) and
 // NT = 1024 threads (<= 4096), so that each thread holds at most 8 (rows) or 16 (columns)
-// complex values per FFT stage and 16 pixels of a row block.  Global memory phases issue all
+// complex values per FFT stage and 16 pixels of a row block.  The row inverse of small single
+// images also runs groups of NT = 128 or 256 threads, one line each (k_rowinv_g).  Global memory phases issue all
 // of a thread's loads before using any of them.
 #pragma once
 
