@@ -446,9 +446,10 @@ int epr_get_timing(epr_handle h, epr_timing* out);
 /* Host-only helpers (no device needed). */
 
 /* Elementary radix sequence of an FFT of length n (a product of 2, 3 and 5: radix 16, then 8, 4
- * or 2, then 5s and 3s; the library transforms the lengths that have one, in these or in fewer
- * stages of composite radices, e.g. 1215 as 15 9 9): writes up to `capacity` radices to `radices` (host) and returns the number of stages, EPR_ERR_SHAPE if n
- * has another prime factor, EPR_ERR_INVALID_ARG for n < 1 or a NULL array with capacity > 0. */
+ * or 2, then 5s and 3s; the library may transform such a length in fewer stages of composite
+ * radices, e.g. 1215 as 15 9 9): writes up to `capacity` radices to `radices` (host) and returns
+ * the number of stages, EPR_ERR_SHAPE if n has another prime factor, EPR_ERR_INVALID_ARG for
+ * n < 1 or a NULL array with capacity > 0. */
 int epr_fft_plan(int32_t n, int32_t* radices, int32_t capacity);
 
 /* Validate a problem description exactly as the solver entry points do, without a device.
